@@ -237,6 +237,28 @@ int streamkl_bwd_act(const void* Q1, const void* K1, const void* Q2, const void*
                      hipStream_t stream);
 
 /*
+ * Backward pass with a choice of the gradients' storage type, for callers
+ * that hand the gradients on in the inputs' bf16 (a training framework whose
+ * parameters are bf16): streamkl_bwd_ex / streamkl_bwd_act with
+ *   bf16_grads  OR of STREAMKL_GRAD_* bits: the gradients stored as bf16
+ *               (contiguous [B,H,N,d], 4-byte aligned). Sums are float32 as
+ *               ever and each value is rounded once, to nearest even, when it
+ *               is written. Gradients without a bit are float32. Bits of
+ *               gradients that are not requested are ignored.
+ * The fused strategy adds into a float32 dQ: with a bf16 dQ requested,
+ * STREAMKL_BWD_FUSED returns STREAMKL_ERR_UNSUPPORTED and STREAMKL_BWD_AUTO
+ * runs the separate kernels. Sigmoid scores run the separate kernels only
+ * (STREAMKL_BWD_FUSED with a dQ: STREAMKL_ERR_UNSUPPORTED).
+ */
+int streamkl_bwd_grads(const void* Q1, const void* K1, const void* Q2, const void* K2,
+                       int B, int H, int N_Q, int N_K, int d1, int d2,
+                       float s1, float s2, int causal, int direction, int activation,
+                       const float* kl, const float* stat1, const float* stat2,
+                       const float* dkl,
+                       void* dQ1, void* dK1, void* dQ2, void* dK2,
+                       int bf16_grads, int strategy, hipStream_t stream);
+
+/*
  * Split-K forward (Sec. 3.3, "Split-K variant" and "Adaptive split
  * selection"): for heads with few query rows, the key range is cut into
  * `splits` contiguous chunks of whole 32-key tiles, each (head, query block,

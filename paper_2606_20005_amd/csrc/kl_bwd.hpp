@@ -55,6 +55,9 @@ struct BwdCfg {
   static_assert(MODE >= 1 && MODE <= 3, "at least one gradient");
 };
 
+// Which gradients are stored as bf16 (BwdArgs::bf16); the others as float32.
+constexpr int kBf16dQb = 1, kBf16dQa = 2, kBf16dKb = 4, kBf16dKa = 8;
+
 // Row statistics in the form the inner loop uses.
 struct RowStats {
   float lsa2, lsb2;  // LSE_a * log2 e, LSE_b * log2 e
@@ -406,16 +409,40 @@ __device__ __forceinline__ void load_resident(bf16x8 (&op)[D / 16], const uint16
 // column 32 nb + l % 32; the factor s of S = s Q K^T is applied here, times
 // row_scale(i) when given. dreal: the row length in global memory (the
 // 32-column blocks past it belong to a padded head dim and are dropped).
+// bf16: the output holds bf16 instead of float32, each value rounded once
+// from its float32 result (the same bits as a cast of the float32 output).
+// Two adjacent lanes then trade values of two adjacent rows, so that each
+// stores one dword (two columns of one row) where it would store two halves.
 template <int D, typename RowScale>
-__device__ __forceinline__ void write_grad(float* out, const f32x16 (&acc)[D / 32], size_t bh_rows, int base,
-                                           int n, float s, int lane, int dreal, RowScale row_scale) {
+__device__ __forceinline__ void write_grad(void* out, bool bf16, const f32x16 (&acc)[D / 32], size_t bh_rows,
+                                           int base, int n, float s, int lane, int dreal, RowScale row_scale) {
   const int half = lane >> 5;
+  if (bf16) {
+    const bool odd = (lane & 1) != 0;
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+      const int row = base + 8 * (i >> 2) + 4 * half + (i & 3) + (lane & 1);   // the row this lane stores
+      const float f0 = s * row_scale(i), f1 = s * row_scale(i + 1);
+      uint32_t* o = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(out) + (bh_rows + row) * dreal + (lane & 30));
+#pragma unroll
+      for (int nb = 0; nb < D / 32; ++nb) {
+        const float v0 = acc[nb][i] * f0, v1 = acc[nb][i + 1] * f1;
+        // DPP quad_perm(1, 0, 3, 2): the value of lane ^ 1
+        const float got = __int_as_float(
+            __builtin_amdgcn_update_dpp(0, __float_as_int(odd ? v0 : v1), 0xB1, 0xF, 0xF, true));
+        const uint16_t lo = __builtin_bit_cast(uint16_t, (__bf16)(odd ? got : v0));
+        const uint16_t hi = __builtin_bit_cast(uint16_t, (__bf16)(odd ? v1 : got));
+        if (row < n && 32 * nb < dreal) o[16 * nb] = (uint32_t)lo | ((uint32_t)hi << 16);
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int row = base + 8 * (i >> 2) + 4 * half + (i & 3);
     if (row < n) {
       const float f = s * row_scale(i);
-      float* o = out + (bh_rows + row) * dreal + (lane & 31);
+      float* o = static_cast<float*>(out) + (bh_rows + row) * dreal + (lane & 31);
 #pragma unroll
       for (int nb = 0; nb < D / 32; ++nb)
         if (32 * nb < dreal) o[32 * nb] = acc[nb][i] * f;
@@ -423,9 +450,9 @@ __device__ __forceinline__ void write_grad(float* out, const f32x16 (&acc)[D / 3
   }
 }
 template <int D>
-__device__ __forceinline__ void write_grad(float* out, const f32x16 (&acc)[D / 32], size_t bh_rows, int base,
-                                           int n, float s, int lane, int dreal = D) {
-  write_grad<D>(out, acc, bh_rows, base, n, s, lane, dreal, [](int) { return 1.f; });
+__device__ __forceinline__ void write_grad(void* out, bool bf16, const f32x16 (&acc)[D / 32], size_t bh_rows,
+                                           int base, int n, float s, int lane, int dreal = D) {
+  write_grad<D>(out, bf16, acc, bh_rows, base, n, s, lane, dreal, [](int) { return 1.f; });
 }
 
 // ----------------------------------------------------------------------------
@@ -438,7 +465,7 @@ kl_bwd_dq_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
                  int NQ, int NK, int dra, int drb, float sa, float sb,
                  const float* __restrict__ kl, const float* __restrict__ lse_a,
                  const float* __restrict__ lse_b, const float* __restrict__ g,
-                 float* __restrict__ dQa, float* __restrict__ dQb) {
+                 void* __restrict__ dQa, void* __restrict__ dQb, int bf16) {
   // PD: the head dims may be padded (the rows in memory are dra, drb long);
   // otherwise they are the compile-time ones and the runtime values unused
   if constexpr (!PD) {
@@ -542,8 +569,8 @@ kl_bwd_dq_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
     rsign[i] = __int_as_float(
         __builtin_amdgcn_ds_bpermute(4 * (8 * (i >> 2) + 4 * half + (i & 3)), __float_as_int(gsign)));
   auto row_sign = [&](int i) { return rsign[i]; };
-  if constexpr (C::WANT_B) write_grad<DB>(dQb, dqb, (size_t)bh * NQ, qw, NQ, sb, lane, drb, row_sign);
-  if constexpr (C::WANT_A) write_grad<DA>(dQa, dqa, (size_t)bh * NQ, qw, NQ, sa, lane, dra, row_sign);
+  if constexpr (C::WANT_B) write_grad<DB>(dQb, bf16 & kBf16dQb, dqb, (size_t)bh * NQ, qw, NQ, sb, lane, drb, row_sign);
+  if constexpr (C::WANT_A) write_grad<DA>(dQa, bf16 & kBf16dQa, dqa, (size_t)bh * NQ, qw, NQ, sa, lane, dra, row_sign);
 }
 
 // ----------------------------------------------------------------------------
@@ -557,7 +584,7 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
                  int NQ, int NK, int dra, int drb, float sa, float sb,
                  const float* __restrict__ kl, const float* __restrict__ lse_a,
                  const float* __restrict__ lse_b, const float* __restrict__ g,
-                 float* __restrict__ dKa, float* __restrict__ dKb,
+                 void* __restrict__ dKa, void* __restrict__ dKb, int bf16,
                  const float* __restrict__ pstats, const int* __restrict__ pfold) {
   // PD: the head dims may be padded (the rows in memory are dra, drb long);
   // otherwise they are the compile-time ones and the runtime values unused
@@ -693,8 +720,8 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
     if (t + 1 < ntq) step(st1, st0, sraw0, sraw1, t + 1, 1);
   }
 
-  if constexpr (C::WANT_B) write_grad<DB>(dKb, dkb, (size_t)bh * NK, kw, NK, sb, lane, drb);
-  if constexpr (C::WANT_A) write_grad<DA>(dKa, dka, (size_t)bh * NK, kw, NK, sa, lane, dra);
+  if constexpr (C::WANT_B) write_grad<DB>(dKb, bf16 & kBf16dKb, dkb, (size_t)bh * NK, kw, NK, sb, lane, drb);
+  if constexpr (C::WANT_A) write_grad<DA>(dKa, bf16 & kBf16dKa, dka, (size_t)bh * NK, kw, NK, sa, lane, dra);
 }
 
 }  // namespace streamkl

@@ -157,7 +157,7 @@ kl_bwd_fused_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict_
                     const float* __restrict__ kl, const float* __restrict__ lse_a,
                     const float* __restrict__ lse_b, const float* __restrict__ g,
                     float* __restrict__ dQa, float* __restrict__ dQb,
-                    float* __restrict__ dKa, float* __restrict__ dKb) {
+                    void* __restrict__ dKa, void* __restrict__ dKb, int bf16) {
   using C = FusedCfg<DA, DB, MODE>;
   using BC = typename C::Base;
   static_assert(C::FITS, "fused backward does not fit in LDS for these head dims");
@@ -419,9 +419,9 @@ kl_bwd_fused_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict_
   }
 
   if constexpr (C::WANT_B)
-    if (dKb) write_grad<DB>(dKb, dkb, (size_t)bh * NK, kw, NK, sb, lane);
+    if (dKb) write_grad<DB>(dKb, bf16 & kBf16dKb, dkb, (size_t)bh * NK, kw, NK, sb, lane);
   if constexpr (C::WANT_A)
-    if (dKa) write_grad<DA>(dKa, dka, (size_t)bh * NK, kw, NK, sa, lane);
+    if (dKa) write_grad<DA>(dKa, bf16 & kBf16dKa, dka, (size_t)bh * NK, kw, NK, sa, lane);
 }
 
 }  // namespace streamkl

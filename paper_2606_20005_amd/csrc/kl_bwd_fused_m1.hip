@@ -14,7 +14,7 @@ static hipError_t run(const BwdArgs& a) {
     const dim3 grid((unsigned)((long long)a.BH * tiles));
     hipLaunchKernelGGL((kl_bwd_fused_kernel<DA, DB, CAUSAL, 1>), grid, dim3(kThreads), 0, a.stream,
                        a.Qa, a.Ka, a.Qb, a.Kb, a.NQ, a.NK, a.sa, a.sb, a.kl, a.lse_a, a.lse_b, a.g,
-                       a.dQa, a.dQb, a.dKa, a.dKb);
+                       static_cast<float*>(a.dQa), static_cast<float*>(a.dQb), a.dKa, a.dKb, a.bf16);
     return hipGetLastError();
   } else {
     return hipErrorNotSupported;

@@ -28,7 +28,8 @@ struct BwdArgs {
   int dra, drb;
   float sa, sb;
   const float *kl, *lse_a, *lse_b, *g;
-  float *dQa, *dQb, *dKa, *dKb;
+  void *dQa, *dQb, *dKa, *dKb;
+  int bf16;                     // which of them hold bf16 (kBf16d* of kl_bwd.hpp), the others float32
   int act;                      // 0: softmax scores; 1: sigmoid scores (kl and the LSEs unused)
   hipStream_t stream;
   // row statistics prepared by launch_bwd_rowstats for the dK kernel (null: it forms them itself)

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdint>
 
+#include "kl_bwd.hpp"
 #include "kl_launch.hpp"
 #include "streamkl.h"
 
@@ -63,8 +64,12 @@ __global__ void zero_fill_kernel(float* __restrict__ p, size_t n) {
     p[i] = 0.f;
 }
 
-hipError_t zero_fill(float* p, size_t n, hipStream_t stream) {
+// n gradient values, float32 or bf16; a count of bf16 values is even (the
+// head dims are multiples of 32).
+hipError_t zero_fill(void* out, size_t n, bool bf16, hipStream_t stream) {
+  float* p = static_cast<float*>(out);
   if (!p || n == 0) return hipSuccess;
+  if (bf16) n /= 2;
   const size_t blocks = (n + 255) / 256;
   hipLaunchKernelGGL(zero_fill_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, stream, p, n);
   return hipGetLastError();
@@ -263,11 +268,13 @@ bool fused_preferred(int N_Q, int N_K) {
 }
 
 // act: STREAMKL_ACT_SOFTMAX or STREAMKL_ACT_SIGMOID (kl, lse1, lse2 unused
-// and not required; separate kernels only).
+// and not required; separate kernels only). bf16_grads: OR of
+// STREAMKL_GRAD_* bits, the gradients stored as bf16 (the fused kernel adds
+// into a float32 dQ, so it takes no bf16 dQ).
 int bwd_common(const void* Q1, const void* K1, const void* Q2, const void* K2, int B, int H, int N_Q, int N_K,
                int d1, int d2, float s1, float s2, int causal, int direction, const float* kl, const float* lse1,
-               const float* lse2, const float* dkl, float* dQ1, float* dK1, float* dQ2, float* dK2, int strategy,
-               int act, hipStream_t stream) {
+               const float* lse2, const float* dkl, void* dQ1, void* dK1, void* dQ2, void* dK2, int bf16_grads,
+               int strategy, int act, hipStream_t stream) {
   if (!dQ1 && !dK1 && !dQ2 && !dK2) return STREAMKL_ERR_INVALID_ARG;
   if (strategy != STREAMKL_BWD_AUTO && strategy != STREAMKL_BWD_SEPARATE && strategy != STREAMKL_BWD_FUSED)
     return STREAMKL_ERR_INVALID_ARG;
@@ -279,8 +286,10 @@ int bwd_common(const void* Q1, const void* K1, const void* Q2, const void* K2, i
   const int kda = kernel_dim(da), kdb = kernel_dim(db);              // the kernels' head dims
   const BwdModes m = bwd_modes(rev, dQ1, dK1, dQ2, dK2);
   const bool sig = act == STREAMKL_ACT_SIGMOID;
+  const bool h_q1 = bf16_grads & STREAMKL_GRAD_DQ1, h_k1 = bf16_grads & STREAMKL_GRAD_DK1;
+  const bool h_q2 = bf16_grads & STREAMKL_GRAD_DQ2, h_k2 = bf16_grads & STREAMKL_GRAD_DK2;
   const bool fused_ok =
-      !sig && m.q != 0 && da == kda && db == kdb && streamkl::bwd_fused_fits(kda, kdb, m.q | m.k);
+      !sig && m.q != 0 && !(dQ1 && h_q1) && !(dQ2 && h_q2) && da == kda && db == kdb && streamkl::bwd_fused_fits(kda, kdb, m.q | m.k);
   if (strategy == STREAMKL_BWD_FUSED && m.q != 0 && !fused_ok) return STREAMKL_ERR_UNSUPPORTED;
   const bool fused = fused_ok && (strategy == STREAMKL_BWD_FUSED ||
                                   (strategy == STREAMKL_BWD_AUTO && fused_preferred(N_Q, N_K)));
@@ -290,8 +299,8 @@ int bwd_common(const void* Q1, const void* K1, const void* Q2, const void* K2, i
   if (N_Q == 0) {
     if ((dK1 && !aligned(dK1, 4)) || (dK2 && !aligned(dK2, 4))) return STREAMKL_ERR_INVALID_ARG;
     hipError_t e = hipSuccess;
-    e = zero_fill(dK1, (size_t)bh * N_K * d1, stream);
-    if (e == hipSuccess) e = zero_fill(dK2, (size_t)bh * N_K * d2, stream);
+    e = zero_fill(dK1, (size_t)bh * N_K * d1, h_k1, stream);
+    if (e == hipSuccess) e = zero_fill(dK2, (size_t)bh * N_K * d2, h_k2, stream);
     return hip_status(e);
   }
   if (!sig && (!kl || !lse1 || !lse2)) return STREAMKL_ERR_INVALID_ARG;
@@ -318,18 +327,20 @@ int bwd_common(const void* Q1, const void* K1, const void* Q2, const void* K2, i
   a.dQb = rev ? dQ1 : dQ2;
   a.dKa = rev ? dK2 : dK1;
   a.dKb = rev ? dK1 : dK2;
+  a.bf16 = ((rev ? h_q1 : h_q2) ? streamkl::kBf16dQb : 0) | ((rev ? h_q2 : h_q1) ? streamkl::kBf16dQa : 0) |
+           ((rev ? h_k1 : h_k2) ? streamkl::kBf16dKb : 0) | ((rev ? h_k2 : h_k1) ? streamkl::kBf16dKa : 0);
   a.act = sig ? 1 : 0;
   a.stream = stream;
   hipError_t e = hipSuccess;
   if (m.q && N_K == 0) {   // every row is empty: zero gradients
-    e = zero_fill(a.dQa, (size_t)bh * N_Q * da, stream);
-    if (e == hipSuccess) e = zero_fill(a.dQb, (size_t)bh * N_Q * db, stream);
+    e = zero_fill(a.dQa, (size_t)bh * N_Q * da, a.bf16 & streamkl::kBf16dQa, stream);
+    if (e == hipSuccess) e = zero_fill(a.dQb, (size_t)bh * N_Q * db, a.bf16 & streamkl::kBf16dQb, stream);
     return hip_status(e);
   }
   if (fused) {
     // dQ accumulates atomically over key blocks: start from zero
-    e = zero_fill(a.dQa, (size_t)bh * N_Q * da, stream);
-    if (e == hipSuccess) e = zero_fill(a.dQb, (size_t)bh * N_Q * db, stream);
+    e = zero_fill(a.dQa, (size_t)bh * N_Q * da, false, stream);
+    if (e == hipSuccess) e = zero_fill(a.dQb, (size_t)bh * N_Q * db, false, stream);
     if (e == hipSuccess) e = streamkl::launch_bwd_fused(kda, kdb, causal == 1, m.q | m.k, a);
     return hip_status(e);
   }
@@ -354,9 +365,9 @@ int bwd_common(const void* Q1, const void* K1, const void* Q2, const void* K2, i
   // the launches; the caller sees only the final dQ.
   float* scratch = nullptr;
   if (m.k && m.q && !sig) {
-    float* dq = a.dQb ? a.dQb : a.dQa;
-    const size_t room = (size_t)bh * N_Q * (a.dQb ? db : da);
-    if (streamkl::bwd_rowstats_floats(a.BH, N_Q) <= room) scratch = dq;
+    const bool half = a.bf16 & (a.dQb ? streamkl::kBf16dQb : streamkl::kBf16dQa);
+    const size_t room = (size_t)bh * N_Q * (a.dQb ? db : da) / (half ? 2 : 1);   // in floats
+    if (streamkl::bwd_rowstats_floats(a.BH, N_Q) <= room) scratch = static_cast<float*>(a.dQb ? a.dQb : a.dQa);
   }
   if (scratch) {
     BwdArgs ak = a;
@@ -377,7 +388,7 @@ extern "C" int streamkl_bwd(const void* Q1, const void* K1, const void* Q2, cons
                             const float* kl, const float* lse1, const float* lse2, const float* dkl, float* dQ1,
                             float* dK1, float* dQ2, float* dK2, hipStream_t stream) {
   return bwd_common(Q1, K1, Q2, K2, B, H, N_Q, N_K, d1, d2, s1, s2, causal, direction, kl, lse1, lse2, dkl, dQ1,
-                    dK1, dQ2, dK2, STREAMKL_BWD_SEPARATE, STREAMKL_ACT_SOFTMAX, stream);
+                    dK1, dQ2, dK2, 0, STREAMKL_BWD_SEPARATE, STREAMKL_ACT_SOFTMAX, stream);
 }
 
 extern "C" int streamkl_bwd_ex(const void* Q1, const void* K1, const void* Q2, const void* K2, int B, int H,
@@ -385,7 +396,7 @@ extern "C" int streamkl_bwd_ex(const void* Q1, const void* K1, const void* Q2, c
                                const float* kl, const float* lse1, const float* lse2, const float* dkl,
                                float* dQ1, float* dK1, float* dQ2, float* dK2, int strategy, hipStream_t stream) {
   return bwd_common(Q1, K1, Q2, K2, B, H, N_Q, N_K, d1, d2, s1, s2, causal, direction, kl, lse1, lse2, dkl, dQ1,
-                    dK1, dQ2, dK2, strategy, STREAMKL_ACT_SOFTMAX, stream);
+                    dK1, dQ2, dK2, 0, strategy, STREAMKL_ACT_SOFTMAX, stream);
 }
 
 extern "C" int streamkl_bwd_act(const void* Q1, const void* K1, const void* Q2, const void* K2, int B, int H,
@@ -394,7 +405,18 @@ extern "C" int streamkl_bwd_act(const void* Q1, const void* K1, const void* Q2, 
                                 const float* dkl, float* dQ1, float* dK1, float* dQ2, float* dK2, hipStream_t stream) {
   if (activation != STREAMKL_ACT_SOFTMAX && activation != STREAMKL_ACT_SIGMOID) return STREAMKL_ERR_INVALID_ARG;
   return bwd_common(Q1, K1, Q2, K2, B, H, N_Q, N_K, d1, d2, s1, s2, causal, direction, kl, stat1, stat2, dkl, dQ1,
-                    dK1, dQ2, dK2, STREAMKL_BWD_SEPARATE, activation, stream);
+                    dK1, dQ2, dK2, 0, STREAMKL_BWD_SEPARATE, activation, stream);
+}
+
+extern "C" int streamkl_bwd_grads(const void* Q1, const void* K1, const void* Q2, const void* K2, int B, int H,
+                                  int N_Q, int N_K, int d1, int d2, float s1, float s2, int causal, int direction,
+                                  int activation, const float* kl, const float* stat1, const float* stat2,
+                                  const float* dkl, void* dQ1, void* dK1, void* dQ2, void* dK2, int bf16_grads,
+                                  int strategy, hipStream_t stream) {
+  if (activation != STREAMKL_ACT_SOFTMAX && activation != STREAMKL_ACT_SIGMOID) return STREAMKL_ERR_INVALID_ARG;
+  if (bf16_grads < 0 || bf16_grads > 15) return STREAMKL_ERR_INVALID_ARG;
+  return bwd_common(Q1, K1, Q2, K2, B, H, N_Q, N_K, d1, d2, s1, s2, causal, direction, kl, stat1, stat2, dkl, dQ1,
+                    dK1, dQ2, dK2, bf16_grads, strategy, activation, stream);
 }
 
 extern "C" int streamkl_bwd_choose(int B, int H, int N_Q, int N_K, int d1, int d2, int causal, int direction,

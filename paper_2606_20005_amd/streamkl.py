@@ -28,7 +28,7 @@ GRAD_BITS = {"dq1": 1, "dk1": 2, "dq2": 4, "dk2": 8}
 ACT_SOFTMAX, ACT_SIGMOID = 0, 1
 ENTRY_POINTS = ("streamkl_fwd", "streamkl_bwd", "streamkl_bwd_ex", "streamkl_bwd_choose", "streamkl_fwd_split",
                 "streamkl_fwd_split_noalloc", "streamkl_fwd_split_workspace_bytes", "streamkl_fwd_split_count",
-                "streamkl_fwd_act", "streamkl_bwd_act", "streamkl_strerror", "streamkl_version",
+                "streamkl_fwd_act", "streamkl_bwd_act", "streamkl_bwd_grads", "streamkl_strerror", "streamkl_version",
                 "streamkl_supported_head_dim")
 
 
@@ -50,6 +50,9 @@ def _load():
     lib.streamkl_bwd_act.argtypes = [vp, vp, vp, vp, i, i, i, i, i, i, f, f, i, i, i, vp, vp, vp, vp, vp, vp, vp,
                                      vp, vp]
     lib.streamkl_bwd_act.restype = i
+    lib.streamkl_bwd_grads.argtypes = [vp, vp, vp, vp, i, i, i, i, i, i, f, f, i, i, i, vp, vp, vp, vp, vp, vp, vp,
+                                       vp, i, i, vp]
+    lib.streamkl_bwd_grads.restype = i
     lib.streamkl_bwd_choose.argtypes = [i, i, i, i, i, i, i, i, i]
     lib.streamkl_bwd_choose.restype = i
     sz = ctypes.c_size_t
@@ -314,6 +317,31 @@ def bwd(q1, k1, q2, k2, kl, lse1, lse2, dkl=None, s1=None, s2=None, causal=False
     return grads["dq1"], grads["dk1"], grads["dq2"], grads["dk2"]
 
 
+def _bwd_bf16(q1, k1, q2, k2, kl, stat1, stat2, g, s1, s2, causal, direction, names, strat, act):
+    """streamkl_bwd_grads: the gradients named in ``names`` in the inputs' bf16, written so by the kernels (a float32
+    gradient and its cast would pass over memory three times more). The fused strategy adds into a float32 dQ, the
+    small side where it applies, which is cast here."""
+    B, H, NQ, d1 = q1.shape
+    NK, d2 = k1.shape[2], q2.shape[3]
+    if strat == BWD_AUTO:
+        strat = BWD_FUSED if bwd_choose(B, H, NQ, NK, d1, d2, causal, direction, names) == "fused" else BWD_SEPARATE
+    dev = q1.device
+    shapes = {"dq1": q1.shape, "dk1": k1.shape, "dq2": q2.shape, "dk2": k2.shape}
+    grads, bits = dict.fromkeys(shapes), 0
+    for n in names:
+        half = strat != BWD_FUSED or n in ("dk1", "dk2")
+        grads[n] = torch.empty(shapes[n], dtype=torch.bfloat16 if half else torch.float32, device=dev)
+        bits |= GRAD_BITS[n] if half else 0
+    with torch.cuda.device(dev):
+        st = lib.streamkl_bwd_grads(_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2, int(bool(causal)),
+                                    _direction(direction), act, _p(kl), _p(stat1), _p(stat2), _p(g),
+                                    _p(grads["dq1"]), _p(grads["dk1"]), _p(grads["dq2"]), _p(grads["dk2"]), bits,
+                                    strat, _stream(dev))
+    if st != OK:
+        raise StreamKLError(st, "streamkl_bwd_grads")
+    return tuple(t if t is None else t.to(torch.bfloat16) for t in grads.values())
+
+
 class _AttentionKL(torch.autograd.Function):
     @staticmethod
     def forward(ctx, q1, k1, q2, k2, s1, s2, causal, direction, bwd_strategy, act):
@@ -335,10 +363,9 @@ class _AttentionKL(torch.autograd.Function):
         if not names:
             return (None,) * 10
         g = gkl.to(torch.float32).contiguous()
-        dq1, dk1, dq2, dk2 = bwd(q1, k1, q2, k2, kl, st1, st2, g, s1, s2, causal, direction, want=names,
-                                 strategy="separate" if act == ACT_SIGMOID else strategy, activation=act)
-        cast = lambda t, ref: None if t is None else t.to(ref.dtype)   # noqa: E731
-        return cast(dq1, q1), cast(dk1, k1), cast(dq2, q2), cast(dk2, k2), None, None, None, None, None, None
+        return (*_bwd_bf16(q1, k1, q2, k2, kl, st1, st2, g, s1, s2, causal, direction, names,
+                           BWD_SEPARATE if act == ACT_SIGMOID else _strategy(strategy), act),
+                None, None, None, None, None, None)
 
 
 def attention_kl(q1, k1, q2, k2, *, s1=None, s2=None, causal=False, direction="fwd", return_lse=False,

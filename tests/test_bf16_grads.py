@@ -1,0 +1,97 @@
+"""streamkl_bwd_grads: gradients stored as bf16 by the kernels are the float32 gradients rounded once (the same bits as a
+cast), whichever kernel writes them; its argument checks; attention_kl's gradients through it."""
+import ctypes
+
+import pytest
+
+from paper_2606_20005_amd import inputs
+
+ALL = ("dq1", "dk1", "dq2", "dk2")
+
+
+def call(sk, t, stats, g, causal, direction, act, grads, bits, strategy):
+    q1, k1, q2, k2 = t
+    B, H, NQ, d1 = q1.shape
+    p = sk._p
+    return sk.lib.streamkl_bwd_grads(p(q1), p(k1), p(q2), p(k2), B, H, NQ, k1.shape[2], d1, q2.shape[3], d1 ** -0.5,
+                                     q2.shape[3] ** -0.5, int(causal), direction, act, *(p(x) for x in stats), p(g),
+                                     *(p(grads[n]) for n in ALL), bits, strategy, sk._stream(q1.device))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("want,strategy,act", [
+    (("dq2", "dk2"), 1, 0), (("dq1", "dk1"), 1, 0), (ALL, 1, 0), (("dk2",), 1, 0), (ALL, 1, 1),
+    (("dk1", "dk2"), 2, 0),   # the fused kernel's dK (with a float32 dQ beside it)
+])
+@pytest.mark.parametrize("nq,nk,d1,d2", [(33, 70, 64, 64), (1, 300, 96, 32), (130, 129, 128, 192), (5, 64, 256, 256)])
+def test_bf16_is_the_rounded_float32(gpu_lib, want, strategy, act, nq, nk, d1, d2):
+    """Odd row counts, tiles with one row, padded head dims, all four gradients in one kernel and in two."""
+    import torch
+    from parity_utils import to_gpu_f32, upload
+    if strategy == 2 and (d1 % 64 or d2 % 64 or d1 + d2 > 320):
+        pytest.skip("no fused kernel for all four gradients at these head dims")
+    d = inputs.make("tiny", B=1, H=2, n_q=nq, n_k=nk, d1=d1, d2=d2, s1=d1 ** -0.5, s2=d2 ** -0.5)
+    t = upload(d)
+    g = to_gpu_f32(d["g"])
+    g[..., ::7] *= -1.0
+    shapes = {"dq1": t[0].shape, "dk1": t[1].shape, "dq2": t[2].shape, "dk2": t[3].shape}
+    for causal, direction in ((True, 0), (False, 1)):
+        stats = gpu_lib.fwd_act(*t, causal=causal, direction=direction, activation=act)
+        asked = ALL if strategy == 2 else want
+        full = {n: torch.full(shapes[n], 7.0, device="cuda") if n in asked else None for n in ALL}
+        half = {n: torch.full(shapes[n], 7.0, device="cuda", dtype=torch.bfloat16 if n in want else torch.float32)
+                if n in asked else None for n in ALL}
+        bits = sum(gpu_lib.GRAD_BITS[n] for n in want)
+        assert call(gpu_lib, t, stats, g, causal, direction, act, full, 0, strategy) == 0
+        assert call(gpu_lib, t, stats, g, causal, direction, act, half, bits, strategy) == 0
+        torch.cuda.synchronize()
+        for n in want:
+            assert torch.equal(half[n].view(torch.int16), full[n].to(torch.bfloat16).view(torch.int16)), n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nq,nk", [(300, 300), (16, 4096), (3, 0), (0, 50)])
+@pytest.mark.parametrize("train", [(2, 3), (0, 1), (0, 1, 2, 3), (3,)])
+def test_attention_kl_gradients(gpu_lib, nq, nk, train):
+    """Separate and fused strategies (the rule picks both here), empty extents: attention_kl's gradients are those of
+    bwd, cast to bf16 (the fused kernel's dQ up to its order of summation)."""
+    import torch
+    from parity_utils import upload
+    if nk == 0 and train == (3,):
+        pytest.skip("the only gradient is empty: no output pointer, an invalid request")
+    t = upload(inputs.make("tiny", B=2, H=2, n_q=nq, n_k=max(nk, 1)))
+    t = [x if nk or i in (0, 2) else x[:, :, :0].contiguous() for i, x in enumerate(t)]
+    for i in train:
+        t[i].requires_grad_(True)
+    kl, l1, l2 = gpu_lib.attention_kl(*t, causal=True, return_lse=True)
+    got = torch.autograd.grad(kl.sum(), [t[i] for i in train])
+    names = [ALL[i] for i in train]
+    u = [x.detach() for x in t]
+    one = torch.ones_like(kl)
+    ref = gpu_lib.bwd(*u, kl.detach(), l1, l2, one, causal=True, want=names, strategy="auto")
+    for n, x in zip(names, got):
+        r = ref[ALL.index(n)].to(torch.bfloat16)
+        assert x.dtype == torch.bfloat16 and x.shape == r.shape
+        if n.startswith("dk"):
+            assert torch.equal(x, r), n
+        else:   # one bf16 step where the sums differ in their last bits
+            assert torch.allclose(x.float(), r.float(), rtol=2 ** -7, atol=1e-6), n
+
+
+def test_argument_checks():
+    from paper_2606_20005_amd import streamkl as sk
+    P = ctypes.c_void_p(0x1000)
+
+    def run(bits=4, strategy=1, act=0, dq2=P, d=64, nq=64):
+        return sk.lib.streamkl_bwd_grads(P, P, P, P, 1, 1, nq, 64, d, d, 0.125, 0.125, 0, 0, act, P, P, P, None, None,
+                                         None, dq2, None, bits, strategy, None)
+    assert run(bits=-1) == sk.ERR_INVALID_ARG
+    assert run(bits=16) == sk.ERR_INVALID_ARG
+    assert run(act=2) == sk.ERR_INVALID_ARG
+    assert run(strategy=3) == sk.ERR_INVALID_ARG
+    assert run(dq2=None) == sk.ERR_INVALID_ARG                     # no gradient requested
+    assert run(dq2=ctypes.c_void_p(0x1002)) == sk.ERR_INVALID_ARG  # 4-byte alignment, also for bf16
+    assert run(strategy=2) == sk.ERR_UNSUPPORTED                   # the fused kernel adds into a float32 dQ
+    assert run(strategy=2, act=1) == sk.ERR_UNSUPPORTED
+    assert run(d=48) == sk.ERR_UNSUPPORTED
+    assert run(nq=0) == sk.OK                                      # nothing to launch
