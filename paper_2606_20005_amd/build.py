@@ -35,6 +35,16 @@ CFLAGS = [
 ]
 
 
+# The pipelined backward keeps one wave per SIMD with all 512 registers, where the compiler by default lets every MFMA
+# write the upper half, which vector instructions cannot read: each logit would be copied down first. This form keeps
+# the logits in the lower half and leaves the resident rows to the upper one.
+UNIT_FLAGS = {"kl_bwd_pipe_": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
+
+def unit_flags(src: str) -> list[str]:
+    return [f for prefix, flags in UNIT_FLAGS.items() if os.path.basename(src).startswith(prefix) for f in flags]
+
+
 def hipcc() -> str:
     for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")):
         if c and os.path.exists(c):
@@ -68,7 +78,7 @@ def build(jobs: int | None = None, verbose: bool = False) -> str:
             for s in allsrc]
     jobs = jobs or min(len(allsrc), max(1, min(16, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        futs = [ex.submit(_run, [cc, *CFLAGS, "-c", s, "-o", o], verbose) for s, o in zip(allsrc, objs)]
+        futs = [ex.submit(_run, [cc, *CFLAGS, *unit_flags(s), "-c", s, "-o", o], verbose) for s, o in zip(allsrc, objs)]
         for f in futs:
             f.result()
     for lib, part in ((LIB, objs[:len(srcs)]), (BENCH_LIB, objs[len(srcs):])):

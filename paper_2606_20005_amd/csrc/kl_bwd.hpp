@@ -141,20 +141,18 @@ __device__ __forceinline__ RowStats tile_row_stats(float la, float lb, float klv
   }
   return s;
 }
-// ... and after it: a tile with no negative g folds |g| into the exponent
-// offsets and stores g = 1, which keeps the unfolded path exact on it.
-__device__ __forceinline__ RowStats finish_tile_row_stats(RowStats s, bool any_negative) {
-  if (!any_negative) {
-    s = fold_row_stats(s);
-    s.g = 1.f;
-  }
+// ... with |g| folded into the exponent offsets; g keeps the sign, 1 or -1.
+__device__ __forceinline__ RowStats finish_tile_row_stats(RowStats s) {
+  const bool negative = s.g < 0.f;
+  s = fold_row_stats(s);
+  s.g = negative ? -1.f : 1.f;
   return s;
 }
 
-// Statistics of a streamed 32-row tile in LDS: [lsa2, lsb2, g, dl][row], and
-// in *fold whether g has been folded into lsa2, lsb2 (every g of the tile
-// >= 0, the usual case; the stored g is then 1): the tile loop may then skip
-// one multiply per distribution and element. Rows at tid >= BS idle.
+// Statistics of a streamed 32-row tile in LDS: [lsa2, lsb2, g, dl][row], |g|
+// folded into lsa2, lsb2, and in *fold whether every stored g is 1 (every g
+// of the tile >= 0, the usual case): the tile loop may then skip one multiply
+// per distribution and element. Rows at tid >= BS idle.
 template <int BS, int ACT = kActSoftmax>
 __device__ __forceinline__ void stage_row_stats(const float (*raw)[64], int r0, int NQ, bool has_g,
                                                 f32x4 (&dst)[4][BS / 4], int* fold, int tid) {
@@ -171,7 +169,7 @@ __device__ __forceinline__ void stage_row_stats(const float (*raw)[64], int r0, 
     s = tile_row_stats(raw[0][tid], raw[1][tid], raw[2][tid], has_g ? raw[3][tid] : 1.f, r0 + tid < NQ);
   const bool any_negative = __builtin_amdgcn_ballot_w64(tid < BS && s.g < 0.f) != 0;
   if (tid < BS) {
-    s = finish_tile_row_stats(s, any_negative);
+    s = finish_tile_row_stats(s);
     float* p = reinterpret_cast<float*>(&dst[0][0]);
     p[0 * BS + tid] = s.lsa2;
     p[1 * BS + tid] = s.lsb2;
@@ -189,8 +187,8 @@ __device__ __forceinline__ void stage_row_stats(const float (*raw)[64], int r0, 
 // tile's barrier. kl_bwd_rowstats_kernel forms them for every tile of every
 // head beforehand, with the same arithmetic bit for bit: tile T = head * ntq
 // + t (ntq = ceil(N_Q / 32)) as stats[T][4][32] floats (lsa2, lsb2, g, dl by
-// row) and fold[T], whether the tile's g are folded (the kernel is in
-// kl_bwd_rowstats.hip). The dK kernel then streams each tile's 512 bytes and
+// row, |g| folded, g the sign) and fold[T], whether every sign is positive
+// (the kernel is in kl_bwd_rowstats.hip). The dK kernel then streams each tile's 512 bytes and
 // flag into LDS with its query tile.
 // ----------------------------------------------------------------------------
 constexpr int kRowStatsTile = 32;
@@ -205,11 +203,16 @@ struct PreparedStatsDma {
     r_s = make_rsrc(on ? stats + head_tile0 * 4 * kRowStatsTile : stats, on ? (uint32_t)ntq * 512u : 0u);
     r_f = make_rsrc(on ? fold + head_tile0 : fold, on ? (uint32_t)ntq * 4u : 0u);
   }
-  __device__ __forceinline__ void issue(int t, float* dst, int* fold_dst, int lane) const {
+  __device__ __forceinline__ void issue_stats(int t, float* dst, int lane) const {
 #if defined(__HIP_DEVICE_COMPILE__)
     const uint32_t off = (uint32_t)t * 512u + (uint32_t)lane * 4u;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r_s, (lds_void*)dst, 4, off, 0, 0, 0);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r_s, (lds_void*)(dst + 64), 4, off + 256u, 0, 0, 0);
+#endif
+  }
+  __device__ __forceinline__ void issue(int t, float* dst, int* fold_dst, int lane) const {
+    issue_stats(t, dst, lane);
+#if defined(__HIP_DEVICE_COMPILE__)
     if (lane == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(r_f, (lds_void*)fold_dst, 4, (uint32_t)t * 4u, 0, 0, 0);
 #endif
   }

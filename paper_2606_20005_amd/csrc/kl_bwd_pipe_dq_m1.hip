@@ -1,0 +1,11 @@
+// Instantiations of the pipelined query-owned dQ backward kernel for gradient mode 1
+// (second-slot distribution (Setting 1)).
+#include "kl_bwd_pipe_launch.hpp"
+
+namespace streamkl {
+
+hipError_t launch_bwd_pipe_dq_m1(int da, int db, bool causal, const BwdArgs& a, bool* taken) {
+  return launch_pipe_unit<1, false>(da, db, causal, a, taken);
+}
+
+}  // namespace streamkl

@@ -1,0 +1,81 @@
+// Launchers of the pipelined backward kernels and the rule that picks them.
+#pragma once
+
+#include "kl_bwd_pipe.hpp"
+#include "kl_launch.hpp"
+
+namespace streamkl {
+
+// Row blocks per wave of the pipelined kernel a call takes, or 0 for the
+// kernel of kl_bwd.hpp. Measured on MI355X, same box, old against new, ms:
+//  - Where the old kernel leaves one wave per SIMD, the pipelined one with one
+//    block is faster at every size, since that one wave overlaps its own
+//    matrix and vector work: wide heads, whose registers allow no second
+//    wave (16 heads x 8192, dQ and dK: d 192/128 1.22, 1.22 -> 1.06, 0.95;
+//    256/256 1.80, 1.66 -> 1.50, 1.46; all four gradients at 128/64 1.14,
+//    1.16 -> 1.02, 0.98), and grids of at most one workgroup per CU (8 heads
+//    x 2048, 128/128: 0.064, 0.071 -> 0.058, 0.059).
+//  - Larger grids give the old kernel two waves per SIMD, which beat one
+//    block (32 x 8192, 128/128: 1.49 against 1.73), but two blocks halve the
+//    operand and tile traffic. Their 256-row workgroups sit alone on a CU, so
+//    nothing hides their start and end: they pay once a workgroup streams
+//    enough rows, and the grid fills the CUs evenly.
+//    dK: from 4096 rows on (8 x 32768 5.75 -> 5.36; 32 x 8192 1.48 -> 1.39,
+//    causal 0.77 -> 0.77; d 192/64 1.43 -> 1.32 and 0.74 -> 0.73; at 32 x 4096
+//    causal 0.22 -> 0.23), over two rounds of workgroups, causal four.
+//    dQ: from 16384 rows on (32 x 16384 5.6 -> 5.35; 8 x 32768 causal 2.75 ->
+//    2.69; 32 x 8192, d 128/64 1.10 -> 1.13), over four rounds, or on an even
+//    grid that fills its rounds (8 x 8192 x 131072, d 192/64 5.13 -> 4.94).
+// The rows a workgroup streams are the mean over the grid: under the causal
+// mask a query row sees N_K - (N_Q - 1) / 2 keys on average.
+template <int DA, int DB, int MODE, bool DK>
+int pipe_blocks(const BwdArgs& a, bool causal) {
+  const long long nq = a.NQ, nk = a.NK, own = DK ? nk : nq;
+  if constexpr (kPipeBuilt<DA, DB, MODE, 2, DK>) {
+    const long long wg = a.BH * ((own + 255) / 256);
+    const long long seen = !causal ? nk : nk >= nq ? nk - nq / 2 : nk / 2;   // keys per query row
+    const long long streamed = DK ? seen * nq / (nk > 0 ? nk : 1) : seen;
+    const bool even = (!causal || nk >= 8 * nq) && 20 * wg >= 19 * ((wg + kCus - 1) / kCus * kCus);
+    if (DK ? streamed >= 4096 && wg >= (causal ? 4 : 2) * kCus : streamed >= 16384 && (wg >= 4 * kCus || even)) return 2;
+  }
+  if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {
+    if (BwdCfg<DA, DB, MODE>::MINB == 1 || a.BH * ((own + 127) / 128) <= kCus) return 1;
+  }
+  return 0;
+}
+
+template <int DA, int DB, bool CAUSAL, int MODE, int RB, bool DK>
+hipError_t run_pipe(const BwdArgs& a) {
+  if constexpr (kPipeBuilt<DA, DB, MODE, RB, DK>) {
+    const long long rows = PipeCfg<DA, DB, MODE, RB>::BR;
+    const dim3 grid((unsigned)(a.BH * (((DK ? a.NK : a.NQ) + rows - 1) / rows)));
+    if constexpr (DK)
+      hipLaunchKernelGGL((kl_bwd_dk_pipe_kernel<DA, DB, CAUSAL, MODE, RB>), grid, dim3(kThreads), 0, a.stream, a.Qa,
+                         a.Ka, a.Qb, a.Kb, a.NQ, a.NK, a.sa, a.sb, a.dKa, a.dKb, a.bf16, a.pstats, a.pfold);
+    else
+      hipLaunchKernelGGL((kl_bwd_dq_pipe_kernel<DA, DB, CAUSAL, MODE, RB>), grid, dim3(kThreads), 0, a.stream, a.Qa,
+                         a.Ka, a.Qb, a.Kb, a.NQ, a.NK, a.sa, a.sb, a.kl, a.lse_a, a.lse_b, a.g, a.dQa, a.dQb, a.bf16);
+    return hipGetLastError();
+  } else {
+    return hipErrorInvalidValue;
+  }
+}
+
+// Launches the pipelined kernel if the rule picks one; taken says whether.
+template <int MODE, bool DK>
+hipError_t launch_pipe_unit(int da, int db, bool causal, const BwdArgs& a, bool* taken) {
+  *taken = false;
+#define STREAMKL_CASE(DA, DB)                                                                                        \
+  if (da == DA && db == DB) {                                                                                        \
+    const int rb = pipe_blocks<DA, DB, MODE, DK>(a, causal);                                                        \
+    *taken = rb != 0;                                                                                                \
+    if (rb == 2) return causal ? run_pipe<DA, DB, true, MODE, 2, DK>(a) : run_pipe<DA, DB, false, MODE, 2, DK>(a);   \
+    if (rb == 1) return causal ? run_pipe<DA, DB, true, MODE, 1, DK>(a) : run_pipe<DA, DB, false, MODE, 1, DK>(a);   \
+    return hipSuccess;                                                                                               \
+  }
+  STREAMKL_FOR_EACH_DIM_PAIR(STREAMKL_CASE)
+#undef STREAMKL_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace streamkl

@@ -22,7 +22,7 @@ kl_bwd_rowstats_kernel(const float* __restrict__ kl, const float* __restrict__ l
   const uint64_t neg = __builtin_amdgcn_ballot_w64(live && s.g < 0.f);
   const bool any_negative = ((neg >> (lane & 32)) & 0xffffffffull) != 0;   // this half-wave's tile
   if (!live) return;
-  s = finish_tile_row_stats(s, any_negative);
+  s = finish_tile_row_stats(s);
   float* p = stats + (size_t)T * 4 * kRowStatsTile;
   p[0 * kRowStatsTile + r] = s.lsa2;
   p[1 * kRowStatsTile + r] = s.lsb2;

@@ -74,6 +74,15 @@ hipError_t launch_bwd_dq_sig_m3(int da, int db, bool causal, const BwdArgs& a);
 hipError_t launch_bwd_dk_sig_m1(int da, int db, bool causal, const BwdArgs& a);
 hipError_t launch_bwd_dk_sig_m2(int da, int db, bool causal, const BwdArgs& a);
 hipError_t launch_bwd_dk_sig_m3(int da, int db, bool causal, const BwdArgs& a);
+// Pipelined forms of the dQ and dK kernels (kl_bwd_pipe.hpp), softmax scores
+// and unpadded head dims only; dK with prepared statistics. *taken: whether
+// the rule for these sizes picked one (if not, nothing was launched).
+hipError_t launch_bwd_pipe_dq_m1(int da, int db, bool causal, const BwdArgs& a, bool* taken);
+hipError_t launch_bwd_pipe_dq_m2(int da, int db, bool causal, const BwdArgs& a, bool* taken);
+hipError_t launch_bwd_pipe_dq_m3(int da, int db, bool causal, const BwdArgs& a, bool* taken);
+hipError_t launch_bwd_pipe_dk_m1(int da, int db, bool causal, const BwdArgs& a, bool* taken);
+hipError_t launch_bwd_pipe_dk_m2(int da, int db, bool causal, const BwdArgs& a, bool* taken);
+hipError_t launch_bwd_pipe_dk_m3(int da, int db, bool causal, const BwdArgs& a, bool* taken);
 // Fused backward (Sec. 4.2): one key-owned kernel writes dK and adds dQ with
 // atomics; dQ must be zeroed first. bwd_fused_fits says whether the kernel
 // exists for these head dims and mode (its working set must fit in LDS).
