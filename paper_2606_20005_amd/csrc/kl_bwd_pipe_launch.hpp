@@ -39,7 +39,7 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
     if (DK ? streamed >= 4096 && wg >= (causal ? 4 : 2) * kCus : streamed >= 16384 && (wg >= 4 * kCus || even)) return 2;
   }
   if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {
-    if (BwdCfg<DA, DB, MODE>::MINB == 1 || a.BH * ((own + 127) / 128) <= kCus) return 1;
+    if (BwdCfg<DA, DB, MODE>::MINB == 1 || a.BH * ((own + 127) / 128) <= (causal ? 2 : 1) * kCus) return 1;
   }
   return 0;
 }

@@ -359,10 +359,14 @@ __device__ __forceinline__ int xcd_logical(int bid, int nb) {
 // up: measured, the rank order took 22% off all three kernels of a 32-head
 // 4K causal grid (two rounds) and 8% off a 16K forward (four rounds), and
 // added 5% to a 64K key-block grid (32 rounds). So it applies up to
-// kRankOrderMaxRounds rounds of `slots` resident workgroups.
+// kRankOrderMaxRounds rounds of `slots` resident workgroups. Heads that do not
+// split evenly over the XCDs are handed out rank by rank over the whole chip:
+// the balance is worth more than the shared L2 there too (12 heads x 16K, d
+// 128/128: dQ 1.20 -> 1.08 ms, dK 1.27 -> 1.18; 20 heads x 8K, d 64/64: 0.34 ->
+// 0.27, 0.44 -> 0.34; 12 heads x 1K the same).
 // Sets the head bh and the rank (0 = longest) of workgroup bid of a grid of
-// nb = heads * T; when the heads do not split evenly over the XCDs, or the
-// grid is longer, the head-by-head order of xcd_logical. Bijective.
+// nb = heads * T; longer grids take the head-by-head order of xcd_logical.
+// Bijective.
 // ---------------------------------------------------------------------------
 constexpr int kCus = 256;                 // MI355X compute units
 constexpr int kRankOrderMaxRounds = 4;
@@ -374,6 +378,9 @@ __device__ __forceinline__ void causal_block(int bid, int nb, int T, int slots, 
     const int x = bid % kXcds, k = bid / kXcds;
     bh = x * hx + k % hx;
     rank = k / hx;
+  } else if (nb <= kRankOrderMaxRounds * slots) {
+    bh = bid % heads;
+    rank = bid / heads;
   } else {
     const int l = xcd_logical(bid, nb);
     bh = l / T;
