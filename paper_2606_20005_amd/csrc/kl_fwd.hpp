@@ -650,32 +650,38 @@ kl_fwd_partial_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restric
   }
 }
 
-// Split-K reduce (Sec. 3.3): one wave per row. Lane w merges partials w,
-// w + 64, ... (independent loads, all in flight together), then the wave
-// merges its 64 lane states by a butterfly of shuffles, and lane 0 writes
-// KL, LSE_a, LSE_b. One thread per row walking its W partials in sequence
-// spent a load latency per partial: 14-20 us at W = 32.
-constexpr int kMergeRowsPerBlock = 4;
-static __global__ void __launch_bounds__(64 * kMergeRowsPerBlock)
-kl_fwd_merge_kernel(const float* __restrict__ part, int W, size_t rows, float* __restrict__ kl,
+// Split-K reduce (Sec. 3.3). L lanes per row, L the power of two that holds W
+// (64 at most): lane l of a wave takes row l % R, R = 64 / L, and partials
+// l / R, l / R + L, ... (independent loads, all in flight together, R rows in
+// a run); the row's L lane states merge by a butterfly of shuffles and its
+// first lane writes KL, LSE_a, LSE_b. What bounds it is the launch and a load
+// latency (W = 32, 1024 rows: 4 us), so lanes without a partial are what
+// counts: a whole wave for two partials took 32 us for 64K rows, 4 us so. One
+// thread per row walking W partials in sequence spent a latency per partial
+// (14-20 us at W = 32).
+constexpr int kMergeWavesPerBlock = 4;
+static __global__ void __launch_bounds__(64 * kMergeWavesPerBlock)
+kl_fwd_merge_kernel(const float* __restrict__ part, int W, int R, size_t rows, float* __restrict__ kl,
                     float* __restrict__ lse_a, float* __restrict__ lse_b) {
   const int lane = threadIdx.x & 63;
-  const size_t ri = (size_t)blockIdx.x * kMergeRowsPerBlock + (threadIdx.x >> 6);
-  if (ri >= rows) return;   // whole waves leave together
+  const int r = lane & (R - 1), w0 = lane / R, L = 64 / R;
+  const size_t ri = ((size_t)blockIdx.x * kMergeWavesPerBlock + (threadIdx.x >> 6)) * R + r;
+  const bool live = ri < rows;
   const size_t plane = (size_t)W * rows;
   RowPartial acc{kNegInf, 0.f, kNegInf, 0.f, 0.f};
-  for (int w = lane; w < W; w += 64) {
-    const size_t i = (size_t)w * rows + ri;
-    acc = merge_partials(acc, RowPartial{part[i], part[i + plane], part[i + 2 * plane], part[i + 3 * plane],
-                                         part[i + 4 * plane]});
+  if (live) {
+    for (int w = w0; w < W; w += L) {
+      const size_t i = (size_t)w * rows + ri;
+      acc = merge_partials(acc, RowPartial{part[i], part[i + plane], part[i + 2 * plane], part[i + 3 * plane],
+                                           part[i + 4 * plane]});
+    }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
+  for (int off = 32; off >= R; off >>= 1) {
     const RowPartial other{__shfl_xor(acc.ma, off), __shfl_xor(acc.la, off), __shfl_xor(acc.mb, off),
                            __shfl_xor(acc.lb, off), __shfl_xor(acc.acc, off)};
     acc = merge_partials(acc, other);
   }
-  if (lane == 0) write_row(acc, ri, kl, lse_a, lse_b);
+  if (live && w0 == 0) write_row(acc, ri, kl, lse_a, lse_b);
 }
 
 // Configuration per head-dim pair: eight waves (256 rows share each key

@@ -26,9 +26,11 @@ static hipError_t run_cfg(const FwdArgs& a, int W, float* part) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t rows = (size_t)a.BH * a.NQ;
-    hipLaunchKernelGGL(kl_fwd_merge_kernel, dim3((unsigned)((rows + kMergeRowsPerBlock - 1) / kMergeRowsPerBlock)),
-                       dim3(64 * kMergeRowsPerBlock), 0, a.stream,
-                       part, W, rows, a.kl, a.lse_a, a.lse_b);
+    int R = 64;   // rows per wave of the merge
+    while (R > 1 && 64 / R < W) R /= 2;
+    const size_t per_block = (size_t)kMergeWavesPerBlock * R;
+    hipLaunchKernelGGL(kl_fwd_merge_kernel, dim3((unsigned)((rows + per_block - 1) / per_block)),
+                       dim3(64 * kMergeWavesPerBlock), 0, a.stream, part, W, R, rows, a.kl, a.lse_a, a.lse_b);
     return hipGetLastError();
   }
 }
@@ -55,7 +57,7 @@ static hipError_t run_fwd(const FwdArgs& a, int W, float* part) {
   return run_cfg<DA, DB, CAUSAL, FwdCfg<DA, DB>>(a, W, part);
 }
 
-int fwd_merge_rows_per_workgroup() { return kMergeRowsPerBlock; }
+int fwd_merge_rows_per_workgroup() { return kMergeWavesPerBlock; }
 
 int fwd_rows_per_workgroup(int da, int db, int n_q, long long bh, bool causal, bool padded) {
   if (padded) return 128;   // FwdPadDimCfg

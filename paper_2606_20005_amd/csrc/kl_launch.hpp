@@ -48,7 +48,7 @@ hipError_t launch_fwd_sigmoid(int da, int db, bool causal, const FwdArgs& a);
 // Query rows per workgroup of the forward for these (kernel) head dims, rows
 // per head, number of heads and mask; padded: the real dims are narrower.
 int fwd_rows_per_workgroup(int da, int db, int n_q, long long bh, bool causal, bool padded);
-// Rows per workgroup of the split-K merge.
+// Rows per workgroup of the split-K merge, at least.
 int fwd_merge_rows_per_workgroup();
 // Kernel head dims d1 + d2 from which the host runs all four gradients as
 // the student-pair kernels followed by the teacher-pair kernels: a kernel
