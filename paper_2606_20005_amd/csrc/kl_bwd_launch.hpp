@@ -41,9 +41,26 @@ hipError_t run_bwd_kernel(bool causal, const BwdArgs& a) {
 // Launches the dQ (DK = false) or dK (DK = true) kernel of gradient mode
 // MODE and activation ACT for the kernel head-dim pair (da, db); the
 // instantiation for padded head dims when the real ones (a.dra, a.drb) are
-// narrower.
+// narrower. Where the rule for the sizes picks the pipelined form of the
+// kernel (softmax scores, unpadded head dims; dK with prepared statistics),
+// that one runs instead.
 template <int MODE, int ACT, bool DK>
 hipError_t launch_bwd_unit(int da, int db, bool causal, const BwdArgs& a) {
+  if constexpr (ACT == kActSoftmax) {
+    if (a.dra == da && a.drb == db && (!DK || a.pstats != nullptr)) {
+      bool taken = false;
+      hipError_t e;
+      if constexpr (DK)
+        e = MODE == 1   ? launch_bwd_pipe_dk_m1(da, db, causal, a, &taken)
+            : MODE == 2 ? launch_bwd_pipe_dk_m2(da, db, causal, a, &taken)
+                        : launch_bwd_pipe_dk_m3(da, db, causal, a, &taken);
+      else
+        e = MODE == 1   ? launch_bwd_pipe_dq_m1(da, db, causal, a, &taken)
+            : MODE == 2 ? launch_bwd_pipe_dq_m2(da, db, causal, a, &taken)
+                        : launch_bwd_pipe_dq_m3(da, db, causal, a, &taken);
+      if (taken || e != hipSuccess) return e;
+    }
+  }
 #define STREAMKL_CASE(DA, DB)                                                                       \
   if (da == DA && db == DB) {                                                                       \
     if constexpr (MODE == 3 && DA + DB >= kSplitPairsDims) {                                        \

@@ -461,13 +461,6 @@ hipError_t launch_bwd_dq(int da, int db, bool causal, int mode, const BwdArgs& a
       default: return hipErrorInvalidValue;
     }
   }
-  if (a.dra == da && a.drb == db) {
-    bool taken = false;
-    const hipError_t e = mode == 1   ? launch_bwd_pipe_dq_m1(da, db, causal, a, &taken)
-                         : mode == 2 ? launch_bwd_pipe_dq_m2(da, db, causal, a, &taken)
-                                     : launch_bwd_pipe_dq_m3(da, db, causal, a, &taken);
-    if (taken || e != hipSuccess) return e;
-  }
   switch (mode) {
     case 1: return launch_bwd_dq_m1(da, db, causal, a);
     case 2: return launch_bwd_dq_m2(da, db, causal, a);
@@ -502,13 +495,6 @@ hipError_t launch_bwd_dk(int da, int db, bool causal, int mode, const BwdArgs& a
       case 3: return launch_bwd_dk_sig_m3(da, db, causal, a);
       default: return hipErrorInvalidValue;
     }
-  }
-  if (a.dra == da && a.drb == db && a.pstats != nullptr) {
-    bool taken = false;
-    const hipError_t e = mode == 1   ? launch_bwd_pipe_dk_m1(da, db, causal, a, &taken)
-                         : mode == 2 ? launch_bwd_pipe_dk_m2(da, db, causal, a, &taken)
-                                     : launch_bwd_pipe_dk_m3(da, db, causal, a, &taken);
-    if (taken || e != hipSuccess) return e;
   }
   switch (mode) {
     case 1: return launch_bwd_dk_m1(da, db, causal, a);
