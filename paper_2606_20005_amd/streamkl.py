@@ -91,11 +91,38 @@ def supported_head_dim(d: int) -> bool:
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # converted by argtypes
 
 
 def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    """The raw current stream of dev, without the Stream object that torch.cuda.current_stream builds (2 us a call)."""
+    return torch._C._cuda_getCurrentRawStream(dev.index)
+
+
+class _SameDevice:
+    """Stands in for torch.cuda.device(dev) where dev is current already (1.5 us a call)."""
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *exc):
+        return False
+
+
+_SAME_DEVICE = _SameDevice()
+
+
+def _on(dev):
+    """Context in which dev is the current device."""
+    return _SAME_DEVICE if torch.cuda.current_device() == dev.index else torch.cuda.device(dev)
+
+
+def _rows3(out, shape, dev, names):
+    """The three row outputs: new ones, or the caller's after a check."""
+    if out is None:
+        return (torch.empty(shape, dtype=torch.float32, device=dev), torch.empty(shape, dtype=torch.float32, device=dev),
+                torch.empty(shape, dtype=torch.float32, device=dev))
+    return tuple(_f32_rows(t, shape, dev, n) for t, n in zip(out, names))
 
 
 def _direction(direction) -> int:
@@ -145,10 +172,8 @@ def fwd(q1, k1, q2, k2, s1=None, s2=None, causal=False, direction=FWD, out=None)
     B, H, NQ, NK, d1, d2 = _check_inputs(q1, k1, q2, k2)
     s1, s2 = _scales(s1, s2, d1, d2)
     dev = q1.device
-    if out is None:
-        out = tuple(torch.empty((B, H, NQ), dtype=torch.float32, device=dev) for _ in range(3))
-    kl, lse1, lse2 = (_f32_rows(t, (B, H, NQ), dev, n) for t, n in zip(out, ("kl", "lse1", "lse2")))
-    with torch.cuda.device(dev):
+    kl, lse1, lse2 = _rows3(out, (B, H, NQ), dev, ("kl", "lse1", "lse2"))
+    with _on(dev):
         st = lib.streamkl_fwd(_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2,
                               int(bool(causal)), _direction(direction), _p(kl), _p(lse1), _p(lse2), _stream(dev))
     if st != OK:
@@ -174,10 +199,8 @@ def fwd_act(q1, k1, q2, k2, s1=None, s2=None, causal=False, direction=FWD, activ
     B, H, NQ, NK, d1, d2 = _check_inputs(q1, k1, q2, k2)
     s1, s2 = _scales(s1, s2, d1, d2)
     dev = q1.device
-    if out is None:
-        out = tuple(torch.empty((B, H, NQ), dtype=torch.float32, device=dev) for _ in range(3))
-    kl, st1, st2 = (_f32_rows(t, (B, H, NQ), dev, n) for t, n in zip(out, ("kl", "stat1", "stat2")))
-    with torch.cuda.device(dev):
+    kl, st1, st2 = _rows3(out, (B, H, NQ), dev, ("kl", "stat1", "stat2"))
+    with _on(dev):
         st = lib.streamkl_fwd_act(_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2, int(bool(causal)),
                                   _direction(direction), _activation(activation), _p(kl), _p(st1), _p(st2),
                                   _stream(dev))
@@ -208,14 +231,15 @@ def fwd_split(q1, k1, q2, k2, s1=None, s2=None, causal=False, direction=FWD, spl
     s1, s2 = _scales(s1, s2, d1, d2)
     dev = q1.device
     w = split_count(B, H, NQ, NK, d1, d2) if splits == "auto" else int(splits)
-    if out is None:
-        out = tuple(torch.empty((B, H, NQ), dtype=torch.float32, device=dev) for _ in range(3))
-    kl, lse1, lse2 = (_f32_rows(t, (B, H, NQ), dev, n) for t, n in zip(out, ("kl", "lse1", "lse2")))
-    need = split_workspace_bytes(B, H, NQ, w)
-    if workspace is None:
-        workspace = torch.empty(max(need, 4), dtype=torch.uint8, device=dev)
-    ws_bytes = workspace.numel() * workspace.element_size()
-    with torch.cuda.device(dev):
+    kl, lse1, lse2 = _rows3(out, (B, H, NQ), dev, ("kl", "lse1", "lse2"))
+    if workspace is not None:
+        ws_bytes = workspace.numel() * workspace.element_size()
+    elif w == 1:   # the single pass needs none
+        ws_bytes = 0
+    else:
+        ws_bytes = max(split_workspace_bytes(B, H, NQ, w), 4)
+        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
+    with _on(dev):
         st = lib.streamkl_fwd_split(_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2,
                                     int(bool(causal)), _direction(direction), w, _p(workspace), ws_bytes,
                                     _p(kl), _p(lse1), _p(lse2), _stream(dev))
@@ -233,10 +257,8 @@ def fwd_split_noalloc(q1, k1, q2, k2, s1=None, s2=None, causal=False, direction=
     s1, s2 = _scales(s1, s2, d1, d2)
     dev = q1.device
     w = split_count(B, H, NQ, NK, d1, d2) if splits == "auto" else int(splits)
-    if out is None:
-        out = tuple(torch.empty((B, H, NQ), dtype=torch.float32, device=dev) for _ in range(3))
-    kl, lse1, lse2 = (_f32_rows(t, (B, H, NQ), dev, n) for t, n in zip(out, ("kl", "lse1", "lse2")))
-    with torch.cuda.device(dev):
+    kl, lse1, lse2 = _rows3(out, (B, H, NQ), dev, ("kl", "lse1", "lse2"))
+    with _on(dev):
         st = lib.streamkl_fwd_split_noalloc(_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2,
                                             int(bool(causal)), _direction(direction), w, _p(kl), _p(lse1),
                                             _p(lse2), _stream(dev))
@@ -303,7 +325,7 @@ def bwd(q1, k1, q2, k2, kl, lse1, lse2, dkl=None, s1=None, s2=None, causal=False
     args = (_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2, int(bool(causal)), _direction(direction),
             _p(kl), _p(lse1), _p(lse2), _p(dkl), _p(grads["dq1"]), _p(grads["dk1"]), _p(grads["dq2"]),
             _p(grads["dk2"]))
-    with torch.cuda.device(dev):
+    with _on(dev):
         if act == ACT_SIGMOID:
             if strat != BWD_SEPARATE:
                 raise ValueError("sigmoid scores run the separate backward kernels only")
@@ -332,7 +354,7 @@ def _bwd_bf16(q1, k1, q2, k2, kl, stat1, stat2, g, s1, s2, causal, direction, na
         half = strat != BWD_FUSED or n in ("dk1", "dk2")
         grads[n] = torch.empty(shapes[n], dtype=torch.bfloat16 if half else torch.float32, device=dev)
         bits |= GRAD_BITS[n] if half else 0
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = lib.streamkl_bwd_grads(_p(q1), _p(k1), _p(q2), _p(k2), B, H, NQ, NK, d1, d2, s1, s2, int(bool(causal)),
                                     _direction(direction), act, _p(kl), _p(stat1), _p(stat2), _p(g),
                                     _p(grads["dq1"]), _p(grads["dk1"]), _p(grads["dq2"]), _p(grads["dk2"]), bits,
