@@ -342,9 +342,11 @@ def bwd(q1, k1, q2, k2, kl, lse1, lse2, dkl=None, s1=None, s2=None, causal=False
 def _bwd_bf16(q1, k1, q2, k2, kl, stat1, stat2, g, s1, s2, causal, direction, names, strat, act):
     """streamkl_bwd_grads: the gradients named in ``names`` in the inputs' bf16, written so by the kernels (a float32
     gradient and its cast would pass over memory three times more). The fused strategy adds into a float32 dQ, the
-    small side where it applies, which is cast here."""
-    B, H, NQ, d1 = q1.shape
-    NK, d2 = k1.shape[2], q2.shape[3]
+    small side where it applies, which is cast here. The tensors are checked again: a saved-tensor hook may have put
+    others in their place since the forward pass."""
+    B, H, NQ, NK, d1, d2 = _check_inputs(q1, k1, q2, k2)
+    kl, stat1, stat2, g = (_f32_rows(t, (B, H, NQ), q1.device, n)
+                           for t, n in ((kl, "kl"), (stat1, "lse1"), (stat2, "lse2"), (g, "dkl")))
     if strat == BWD_AUTO:
         strat = BWD_FUSED if bwd_choose(B, H, NQ, NK, d1, d2, causal, direction, names) == "fused" else BWD_SEPARATE
     dev = q1.device

@@ -78,6 +78,38 @@ def test_attention_kl_gradients(gpu_lib, nq, nk, train):
             assert torch.allclose(x.float(), r.float(), rtol=2 ** -7, atol=1e-6), n
 
 
+def test_backward_refuses_tensors_that_do_not_fit():
+    """A saved-tensor hook can hand the backward pass other tensors than the forward pass saved: each is checked before
+    its pointer is used (here by shape, type and device alone, so without a GPU)."""
+    from types import SimpleNamespace
+
+    import torch
+    from paper_2606_20005_amd import streamkl as sk
+
+    class OnGpu(torch.Tensor):
+        is_cuda = True
+
+    def rows(*shape):
+        return torch.zeros(shape)
+
+    def bf16(*shape):
+        return torch.zeros(shape, dtype=torch.bfloat16).as_subclass(OnGpu)
+
+    good = [bf16(1, 1, 8, 64), bf16(1, 1, 9, 64), bf16(1, 1, 8, 32), bf16(1, 1, 9, 32), *(rows(1, 1, 8) for _ in range(4))]
+    reached = SimpleNamespace(streamkl_bwd_grads=lambda *a: pytest.fail("reached the library"))
+    for i, bad in ((0, torch.zeros(1, 1, 8, 64)), (1, good[1].float()), (2, bf16(1, 1, 32, 8).transpose(2, 3)),
+                   (3, bf16(1, 1, 8, 32)), (4, rows(1, 1, 7)), (5, rows(1, 1, 8).double()), (6, rows(1, 8, 2)[..., :1]),
+                   (7, rows(8))):
+        args = list(good)
+        args[i] = bad
+        lib, sk.lib = sk.lib, reached
+        try:
+            with pytest.raises(ValueError):
+                sk._bwd_bf16(*args, 0.125, 0.125, False, sk.FWD, ["dq2", "dk2"], sk.BWD_SEPARATE, sk.ACT_SOFTMAX)
+        finally:
+            sk.lib = lib
+
+
 def test_argument_checks():
     from paper_2606_20005_amd import streamkl as sk
     P = ctypes.c_void_p(0x1000)
