@@ -212,6 +212,15 @@ def test_causal_rank_order_grids(gpu_lib, H, n, d1, d2):
     run_case(gpu_lib, d, True, 1, want=("dq1", "dk1", "dq2", "dk2"))
 
 
+@pytest.mark.parametrize("H,n,d1,d2", [(1, 300, 128, 64), (5, 333, 64, 64), (12, 260, 128, 128)])
+def test_causal_rank_order_any_heads(gpu_lib, H, n, d1, d2):
+    """Head counts that do not split evenly over the 8 XCDs are handed out rank
+    by rank over the whole chip: as test_causal_rank_order_grids."""
+    d = inputs.make("distill", B=1, H=H, n_q=n, n_k=n, d1=d1, d2=d2, s1=d1 ** -0.5, s2=d2 ** -0.5)
+    run_case(gpu_lib, d, True, 0)
+    run_case(gpu_lib, d, True, 1, want=("dq1", "dk1", "dq2", "dk2"))
+
+
 def test_causal_eight_wave_forward_reduced(gpu_lib):
     """1024 heads of 256 rows: B*H*ceil(N_Q/256) = 1024 workgroups, enough that
     the causal forward takes its eight-wave, 256-row configuration (the one the

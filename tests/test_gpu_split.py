@@ -91,3 +91,18 @@ def test_autograd_uses_split_for_few_rows(gpu_lib):
     for name, got, r in (("dq2", q2.grad, ref[5]), ("dk2", k2.grad, ref[6])):
         g = got.float().cpu().numpy()
         assert np.linalg.norm(g - r) <= 1e-2 * np.linalg.norm(r), name
+
+
+@pytest.mark.parametrize("splits", [2, 3, 16, 17, 33, 64, 65, 130])
+@pytest.mark.parametrize("n_q", [1, 7, 65])
+def test_merge_lanes_follow_the_split_count(gpu_lib, splits, n_q):
+    """The merge gives a row 2, 4, ..., 64 lanes (powers of two around every edge, more partials than lanes) and a wave
+    64 down to 1 rows, the last wave partly filled: every row against the single pass, which merges nothing."""
+    import torch
+    d = inputs.make("tiny", B=1, H=3, n_q=n_q, n_k=4200)
+    w = d["w"]
+    got, (q1, k1, q2, k2) = run_split(gpu_lib, d, False, 0, splits)
+    one = [t.cpu().numpy() for t in gpu_lib.fwd(q1, k1, q2, k2, w.s1, w.s2, False, 0)]
+    torch.cuda.synchronize()
+    for a, b in zip(got, one):   # the merge reorders fp32 sums: same value up to rounding
+        assert np.allclose(a, b, rtol=2e-5, atol=2e-5), float(np.max(np.abs(a - b)))
