@@ -62,8 +62,8 @@ PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBPS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 EVICT_BYTES = 512 << 20        # twice the 256 MB MALL
-KERNEL_NAMES = {"fwd": "kl_fwd_kernel<128,128>", "dq": "kl_bwd_dq_kernel<128,128,mode1>",
-                "dk": "kl_bwd_dk_kernel<128,128,mode1>"}
+KERNEL_NAMES = {"fwd": "kl_fwd_kernel<128,128>", "dq": "kl_bwd_dq_pipe_kernel<128,128,mode1,2>",
+                "dk": "kl_bwd_dk_pipe_kernel<128,128,mode1,2>"}
 
 
 def kernel_source_hash():

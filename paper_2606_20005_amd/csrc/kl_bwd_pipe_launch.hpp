@@ -14,7 +14,9 @@ namespace streamkl {
 //    wave (16 heads x 8192, dQ and dK: d 192/128 1.22, 1.22 -> 1.06, 0.95;
 //    256/256 1.80, 1.66 -> 1.50, 1.46; all four gradients at 128/64 1.14,
 //    1.16 -> 1.02, 0.98), and grids of at most one workgroup per CU (8 heads
-//    x 2048, 128/128: 0.064, 0.071 -> 0.058, 0.059).
+//    x 2048, 128/128: 0.064, 0.071 -> 0.058, 0.059); causal grids, handed out
+//    longest block first, of at most two (causal step of 4 heads, 2000 rows
+//    on 40000 keys, 1.185 -> 1.090).
 //  - Larger grids give the old kernel two waves per SIMD, which beat one
 //    block (32 x 8192, 128/128: 1.49 against 1.73), but two blocks halve the
 //    operand and tile traffic. Their 256-row workgroups sit alone on a CU, so
@@ -36,7 +38,8 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
     const long long seen = !causal ? nk : nk >= nq ? nk - nq / 2 : nk / 2;   // keys per query row
     const long long streamed = DK ? seen * nq / (nk > 0 ? nk : 1) : seen;
     const bool even = (!causal || nk >= 8 * nq) && 20 * wg >= 19 * ((wg + kCus - 1) / kCus * kCus);
-    if (DK ? streamed >= 4096 && wg >= (causal ? 4 : 2) * kCus : streamed >= 16384 && (wg >= 4 * kCus || even)) return 2;
+    if (DK ? streamed >= 4096 && wg >= (causal ? 4 : 2) * kCus : streamed >= 16384 && (wg >= 4 * kCus || even))
+      return 2;
   }
   if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {
     if (BwdCfg<DA, DB, MODE>::MINB == 1 || a.BH * ((own + 127) / 128) <= (causal ? 2 : 1) * kCus) return 1;

@@ -289,7 +289,8 @@ int bwd_common(const void* Q1, const void* K1, const void* Q2, const void* K2, i
   const bool h_q1 = bf16_grads & STREAMKL_GRAD_DQ1, h_k1 = bf16_grads & STREAMKL_GRAD_DK1;
   const bool h_q2 = bf16_grads & STREAMKL_GRAD_DQ2, h_k2 = bf16_grads & STREAMKL_GRAD_DK2;
   const bool fused_ok =
-      !sig && m.q != 0 && !(dQ1 && h_q1) && !(dQ2 && h_q2) && da == kda && db == kdb && streamkl::bwd_fused_fits(kda, kdb, m.q | m.k);
+      !sig && m.q != 0 && !(dQ1 && h_q1) && !(dQ2 && h_q2) && da == kda && db == kdb &&
+      streamkl::bwd_fused_fits(kda, kdb, m.q | m.k);
   if (strategy == STREAMKL_BWD_FUSED && m.q != 0 && !fused_ok) return STREAMKL_ERR_UNSUPPORTED;
   const bool fused = fused_ok && (strategy == STREAMKL_BWD_FUSED ||
                                   (strategy == STREAMKL_BWD_AUTO && fused_preferred(N_Q, N_K)));
