@@ -32,7 +32,8 @@
 //    causal 4.72, 5.47 -> 4.26, 4.73. The outputs are the same bit for bit.
 //
 // Masked pairs: their raw logits are replaced by kBwdMaskedRaw, which gives
-// P = 0 exactly and finite factors, so their logit gradients are 0. Before
+// P = 0 exactly and finite factors at the scales that pipe_scale admits, so
+// their logit gradients are 0. Before
 // the first tile the pipeline holds a neutral one (every pair masked,
 // operands 0).
 #pragma once

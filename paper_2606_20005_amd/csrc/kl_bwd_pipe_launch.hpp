@@ -6,6 +6,13 @@
 
 namespace streamkl {
 
+// Scales that the finite stand-in for masked logits (kBwdMaskedRaw) serves:
+// times the scale it must lie far below any real logit (|q.k| < 1e29) and the
+// log2 |g| beside it, and two such products must add up within the float32
+// range. A call with another scale takes the kernel of kl_bwd.hpp, which
+// selects a zero for every masked pair.
+inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
+
 // Row blocks per wave of the pipelined kernel a call takes, or 0 for the
 // kernel of kl_bwd.hpp. Measured on MI355X, same box, old against new, ms:
 //  - Where the old kernel leaves one wave per SIMD, the pipelined one with one
@@ -32,6 +39,7 @@ namespace streamkl {
 // mask a query row sees N_K - (N_Q - 1) / 2 keys on average.
 template <int DA, int DB, int MODE, bool DK>
 int pipe_blocks(const BwdArgs& a, bool causal) {
+  if (!pipe_scale(a.sa) || !pipe_scale(a.sb)) return 0;
   const long long nq = a.NQ, nk = a.NK, own = DK ? nk : nq;
   if constexpr (kPipeBuilt<DA, DB, MODE, 2, DK>) {
     const long long wg = a.BH * ((own + 255) / 256);

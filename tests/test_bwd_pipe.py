@@ -3,14 +3,34 @@ bit. A head's gradients do not depend on how many heads a call holds, while the 
 256 workgroups of 128 rows take the pipelined form with one row block per wave, more take the plain one, and many
 workgroups of 256 rows the pipelined form with two."""
 import concurrent.futures as cf
+import os
 import re
 import subprocess
 
+import numpy as np
 import pytest
 
-from paper_2606_20005_amd import build
+import oracle
+from paper_2606_20005_amd import build, inputs
+from parity_utils import check_grad, to_gpu_f32, upload
 
 ALL = ("dq1", "dk1", "dq2", "dk2")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    """The host's rule itself: rule(kernel, want, d1, d2, heads, nq, nk, causal) is 0 for the plain kernel of a call
+    without reversed direction, else the pipelined kernel's row blocks per wave."""
+    exe = str(tmp_path_factory.mktemp("rule") / "pipe_rule")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "pipe_rule.hip")
+    r = subprocess.run([build.hipcc(), *build.CFLAGS, "--offload-host-only", src, "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def ask(kernel, want, d1, d2, heads, nq, nk, causal, s1=0.125, s2=0.125):
+        mode = (1 if "dq2" in want else 0) | (2 if "dq1" in want else 0)
+        line = f"{int(kernel == 'dk')} {mode} {d1} {d2} {heads} {nq} {nk} {int(causal)} {s1:.9g} {s2:.9g}\n"
+        return int(subprocess.run([exe], input=line, capture_output=True, text=True, check=True).stdout)
+    return ask
 
 
 def test_no_spills(tmp_path):
@@ -88,3 +108,29 @@ def test_wide_heads_key_gradients_match_the_plain_kernel(gpu_lib, d1, d2, want, 
     for n, a, b in zip(ALL, both, alone):
         if n.startswith("dk") and n in want:
             assert torch.equal(a, b), n
+
+
+EXTREME_SCALES = [   # s1, s2 and the factor on Q and K that keeps the logits of order one
+    (2.0 ** -98, 2.0 ** -102, 2.0 ** 45), (2.0 ** 30, 2.0 ** 29, 2.0 ** -16)]
+
+
+def test_extreme_scales_take_the_plain_kernels(rule):
+    for kernel in ("dq", "dk"):
+        assert rule(kernel, ("dq2", "dk2"), 64, 64, 2, 600, 600, True) == 1
+        for s1, s2, _ in EXTREME_SCALES:
+            assert rule(kernel, ("dq2", "dk2"), 64, 64, 2, 600, 600, True, s1=s1) == 0
+            assert rule(kernel, ("dq2", "dk2"), 64, 64, 2, 600, 600, True, s2=s2) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("s1,s2,factor", EXTREME_SCALES)
+def test_masked_pairs_at_extreme_scales(gpu_lib, s1, s2, factor):
+    """The header admits every finite scale above 0. At these the stand-in for a masked logit would be of the order of
+    the logits (a masked key then takes part) or overflow (0 x inf); backward on statistics computed elsewhere."""
+    d = inputs.make("tiny", B=1, H=2, n_q=600, n_k=600, s1=s1, s2=s2)
+    for n in ("Q1", "K1", "Q2", "K2"):
+        d[n] = d[n] * np.float32(factor)   # exact in bf16
+    kl, lse1, lse2, *ref = oracle.backward(d["Q1"], d["K1"], d["Q2"], d["K2"], s1, s2, True, 0, d["g"])
+    got = gpu_lib.bwd(*upload(d), *(to_gpu_f32(x) for x in (kl, lse1, lse2, d["g"])), s1, s2, True, 0, want=ALL)
+    for n, x, r in zip(ALL, got, ref):
+        check_grad(n, x.cpu().numpy(), r)
