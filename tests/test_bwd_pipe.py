@@ -122,6 +122,17 @@ def test_extreme_scales_take_the_plain_kernels(rule):
             assert rule(kernel, ("dq2", "dk2"), 64, 64, 2, 600, 600, True, s2=s2) == 0
 
 
+STUDENT, TEACHER = ("dq2", "dk2"), ("dq1", "dk1")
+
+
+@pytest.mark.parametrize("d1,d2", [(128, 64), (192, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("heads,nq,nk", [(1024, 8300, 290), (256, 8192, 1024), (64, 20000, 4000)])
+def test_causal_rows_without_a_key_are_not_streamed(rule, heads, nq, nk, d1, d2):
+    """A key of a causal head with nk < nq streams nk / 2 rows on average, however many rows there are."""
+    assert rule("dk", STUDENT, d1, d2, heads, nq, nk, True) == 0
+    assert rule("dk", STUDENT, d1, d2, heads, nq, nk, False) == 2
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("s1,s2,factor", EXTREME_SCALES)
 def test_masked_pairs_at_extreme_scales(gpu_lib, s1, s2, factor):
