@@ -40,6 +40,13 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 // N_K query rows see a key, so that a key streams N_K / 2 of them: two blocks
 // took 1367 us where the old kernel takes 1232 (backward of 1024 heads x 8300
 // rows on 290 keys, d 128/64).
+//  - One block starts and drains its pipeline around the stream (dK also looks
+//    through the flags of its tiles), which a short stream does not pay back.
+//    Kernel times over the old kernel's, mean of a random sweep of grids within
+//    one round, by streamed rows: dK 64-127 1.12 causal, 1.03 not; 128-255
+//    1.03, 0.99; 256-511 0.95, 0.93; 512-1023 0.88. dQ 64-127 1.01; 128-255
+//    0.96, 0.98. Where the old kernel has one wave per SIMD: dK 64-127 1.06,
+//    0.99; 128-255 0.94, 0.97; dQ 0.93 at most, however short.
 template <int DA, int DB, int MODE, bool DK>
 int pipe_blocks(const BwdArgs& a, bool causal) {
   if (!pipe_scale(a.sa) || !pipe_scale(a.sb)) return 0;
@@ -54,7 +61,9 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
       return 2;
   }
   if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {
-    if (BwdCfg<DA, DB, MODE>::MINB == 1 || a.BH * ((own + 127) / 128) <= (causal ? 2 : 1) * kCus) return 1;
+    constexpr bool alone = BwdCfg<DA, DB, MODE>::MINB == 1;
+    if (streamed < (DK ? (alone ? 128 : 256) : (alone ? 0 : 128))) return 0;
+    if (alone || a.BH * ((own + 127) / 128) <= (causal ? 2 : 1) * kCus) return 1;
   }
   return 0;
 }

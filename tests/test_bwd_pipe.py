@@ -133,6 +133,16 @@ def test_causal_rows_without_a_key_are_not_streamed(rule, heads, nq, nk, d1, d2)
     assert rule("dk", STUDENT, d1, d2, heads, nq, nk, False) == 2
 
 
+@pytest.mark.parametrize("d1,d2,alone", [(128, 128, False), (64, 64, False), (256, 256, True), (128, 192, True)])
+def test_short_streams_take_the_plain_kernels(rule, d1, d2, alone):
+    """One block starts to pay from 256 streamed rows for dK and 128 for dQ; where the plain kernel has one wave per SIMD,
+    from 128 and at once."""
+    for n, dq, dk in ((1000, 1, 1), (256, 1, 1), (255, 1, int(alone)), (128, 1, int(alone)), (127, int(alone), 0),
+                      (1, int(alone), 0)):
+        assert rule("dq", STUDENT, d1, d2, 8, 300, n, False) == dq, n
+        assert rule("dk", STUDENT, d1, d2, 8, n, 300, False) == dk, n
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("s1,s2,factor", EXTREME_SCALES)
 def test_masked_pairs_at_extreme_scales(gpu_lib, s1, s2, factor):
