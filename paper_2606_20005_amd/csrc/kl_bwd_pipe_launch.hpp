@@ -21,9 +21,18 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 //    wave (16 heads x 8192, dQ and dK: d 192/128 1.22, 1.22 -> 1.06, 0.95;
 //    256/256 1.80, 1.66 -> 1.50, 1.46; all four gradients at 128/64 1.14,
 //    1.16 -> 1.02, 0.98), and grids of at most one workgroup per CU (8 heads
-//    x 2048, 128/128: 0.064, 0.071 -> 0.058, 0.059); causal grids, handed out
-//    longest block first, of at most two (causal step of 4 heads, 2000 rows
-//    on 40000 keys, 1.185 -> 1.090).
+//    x 2048, 128/128: 0.064, 0.071 -> 0.058, 0.059).
+//  - Causal grids are handed out longest block first, at most two workgroups
+//    to a CU. The old kernel runs both at once, the pipelined one in turn: it
+//    is done with its longest block if the blocks that follow each other are
+//    hardly longer than that together (the middle of the ranks is the longest
+//    such pair; a start counts as 256 rows). Kernel times over the old
+//    kernel's, mean of the sweep by the length of that pair over the longest
+//    block: below 0.5 0.84 (dK) and 0.90 (dQ), 0.5-1 0.86 and 0.87, 1-1.1 0.92
+//    and 1.00 (16 heads x 4096, where it is 1: 0.275 -> 0.244 and 0.265 ->
+//    0.244 a backward), 1.1-1.5 1.16 and 1.02, above 1.18 and 1.15 (blocks of
+//    nearly one length: 12 heads, 5000 rows on 60000 keys, d 64/128, 4.19 ->
+//    4.65).
 //  - Larger grids give the old kernel two waves per SIMD, which beat one
 //    block (32 x 8192, 128/128: 1.49 against 1.73), but two blocks halve the
 //    operand and tile traffic. Their 256-row workgroups sit alone on a CU, so
@@ -63,7 +72,12 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
   if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {
     constexpr bool alone = BwdCfg<DA, DB, MODE>::MINB == 1;
     if (streamed < (DK ? (alone ? 128 : 256) : (alone ? 0 : 128))) return 0;
-    if (alone || a.BH * ((own + 127) / 128) <= (causal ? 2 : 1) * kCus) return 1;
+    const long long wg = a.BH * ((own + 127) / 128);
+    if (alone || wg <= kCus) return 1;
+    if (causal && wg <= 2 * kCus) {
+      const long long after = nk - 128 * (kCus / a.BH), cap = DK ? nq : nk;   // block that the first freed CU takes
+      if (10 * (2 * (after < 0 ? 0 : after < cap ? after : cap) + 256) <= 11 * (nk < cap ? nk : cap)) return 1;
+    }
   }
   return 0;
 }

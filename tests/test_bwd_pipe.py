@@ -143,6 +143,22 @@ def test_short_streams_take_the_plain_kernels(rule, d1, d2, alone):
         assert rule("dk", STUDENT, d1, d2, 8, n, 300, False) == dk, n
 
 
+def test_causal_grids_over_one_round(rule):
+    """Two workgroups to a CU: one after the other pays where their lengths differ enough (square heads), not where the
+    blocks are of nearly one length (the last rows of a long context)."""
+    for kernel in ("dq", "dk"):
+        for heads, n in ((16, 4096), (8, 8192), (12, 4096), (4, 16384)):
+            assert rule(kernel, STUDENT, 128, 128, heads, n, n, True) == 1, (kernel, heads, n)
+            assert rule(kernel, STUDENT, 128, 128, heads, n, n, False) != 1, (kernel, heads, n)
+        for heads, n in ((256, 256), (128, 512), (62, 979), (49, 1204)):   # the second start is not paid back
+            assert rule(kernel, STUDENT, 128, 128, heads, n, n, True) == 0, (kernel, heads, n)
+        assert rule(kernel, STUDENT, 128, 128, 8, 4096, 4096, True) == 1
+    for heads, nq, nk in ((12, 5000, 60000), (8, 8192, 131072), (32, 2048, 36096)):
+        assert rule("dq", STUDENT, 64, 128, heads, nq, nk, True) == 0
+    for heads, nq, nk in ((7, 400, 8000), (16, 600, 4096)):
+        assert rule("dk", STUDENT, 128, 128, heads, nq, nk, True) == 0
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("s1,s2,factor", EXTREME_SCALES)
 def test_masked_pairs_at_extreme_scales(gpu_lib, s1, s2, factor):
