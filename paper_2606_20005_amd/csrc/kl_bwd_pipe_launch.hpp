@@ -16,8 +16,8 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 // Row blocks per wave of the pipelined kernel a call takes, or 0 for the
 // kernel of kl_bwd.hpp. Measured on MI355X, same box, old against new, ms:
 //  - Where the old kernel leaves one wave per SIMD, the pipelined one with one
-//    block is faster at every size, since that one wave overlaps its own
-//    matrix and vector work: wide heads, whose registers allow no second
+//    block is faster (short streams apart, below), since that one wave overlaps
+//    its own matrix and vector work: wide heads, whose registers allow no second
 //    wave (16 heads x 8192, dQ and dK: d 192/128 1.22, 1.22 -> 1.06, 0.95;
 //    256/256 1.80, 1.66 -> 1.50, 1.46; all four gradients at 128/64 1.14,
 //    1.16 -> 1.02, 0.98), and grids of at most one workgroup per CU (8 heads
@@ -37,18 +37,21 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 //    block (32 x 8192, 128/128: 1.49 against 1.73), but two blocks halve the
 //    operand and tile traffic. Their 256-row workgroups sit alone on a CU, so
 //    nothing hides their start and end: they pay once a workgroup streams
-//    enough rows, and the grid fills the CUs evenly.
-//    dK: from 4096 rows on (8 x 32768 5.75 -> 5.36; 32 x 8192 1.48 -> 1.39,
-//    causal 0.77 -> 0.77; d 192/64 1.43 -> 1.32 and 0.74 -> 0.73; at 32 x 4096
-//    causal 0.22 -> 0.23), over two rounds of workgroups, causal four.
-//    dQ: from 16384 rows on (32 x 16384 5.6 -> 5.35; 8 x 32768 causal 2.75 ->
-//    2.69; 32 x 8192, d 128/64 1.10 -> 1.13), over four rounds, or on an even
-//    grid that fills its rounds (8 x 8192 x 131072, d 192/64 5.13 -> 4.94).
-// The rows a workgroup streams are the mean over the grid, a head's allowed
-// pairs over its own rows. Under the causal mask with N_K < N_Q only the last
-// N_K query rows see a key, so that a key streams N_K / 2 of them: two blocks
-// took 1367 us where the old kernel takes 1232 (backward of 1024 heads x 8300
-// rows on 290 keys, d 128/64).
+//    enough rows. What they save is power as much as cycles, so each form was
+//    timed over 80 ms of whole backward passes (1423 grids on two boxes; time
+//    over the old kernels', mean and largest, by the head dim whose gradients
+//    are formed and the other one):
+//      no mask   64 and 128, 192, 256: 0.98, 0.97, 0.95 (1.01); 128 and 128
+//                0.98 (1.02, and one of 1.18), 128 and 64 1.00 (1.05);
+//      causal    64 and 128, 192, 256: 0.98, 0.98, 0.96 (1.03) with the rule
+//                below; 128 and 128 1.01 (1.07), 128 and 64 1.02 (1.09) with
+//                dK alone from 4096 rows on: not taken.
+//    dK: from 4096 rows on, over two rounds of workgroups, causal four.
+//    dQ without a mask: from 16384 rows on, over four rounds or on a grid that
+//    fills its last one to 95% (below four rounds 0.98 (1.00) where it does,
+//    1.05 (1.26) below 85%). dQ causal: from 6144 rows on, over four rounds;
+//    square heads of 6K to 12K streamed rows took 0.99 (1.05) with dK alone and
+//    0.97 (1.03) with both, all heads of 2K to 6K 0.99 (1.04) and 1.00 (1.23).
 //  - One block starts and drains its pipeline around the stream (dK also looks
 //    through the flags of its tiles), which a short stream does not pay back.
 //    Kernel times over the old kernel's, mean of a random sweep of grids within
@@ -56,6 +59,11 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 //    1.03, 0.99; 256-511 0.95, 0.93; 512-1023 0.88. dQ 64-127 1.01; 128-255
 //    0.96, 0.98. Where the old kernel has one wave per SIMD: dK 64-127 1.06,
 //    0.99; 128-255 0.94, 0.97; dQ 0.93 at most, however short.
+// The rows a workgroup streams are the mean over the grid, a head's allowed
+// pairs over its own rows. Under the causal mask with N_K < N_Q only the last
+// N_K query rows see a key, so that a key streams N_K / 2 of them: two blocks
+// took 1367 us where the old kernel takes 1232 (backward of 1024 heads x 8300
+// rows on 290 keys, d 128/64).
 template <int DA, int DB, int MODE, bool DK>
 int pipe_blocks(const BwdArgs& a, bool causal) {
   if (!pipe_scale(a.sa) || !pipe_scale(a.sb)) return 0;
@@ -65,8 +73,11 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
   const long long streamed = own > 0 ? pairs / own : 0;
   if constexpr (kPipeBuilt<DA, DB, MODE, 2, DK>) {
     const long long wg = a.BH * ((own + 255) / 256);
-    const bool even = (!causal || nk >= 8 * nq) && 20 * wg >= 19 * ((wg + kCus - 1) / kCus * kCus);
-    if (DK ? streamed >= 4096 && wg >= (causal ? 4 : 2) * kCus : streamed >= 16384 && (wg >= 4 * kCus || even))
+    const bool even = 20 * wg >= 19 * ((wg + kCus - 1) / kCus * kCus);
+    constexpr bool narrow = MODE == 1 ? DB < DA : DA < DB;
+    if (DK       ? streamed >= 4096 && (causal ? narrow && wg >= 4 * kCus : wg >= 2 * kCus)
+        : causal ? streamed >= 6144 && narrow && wg >= 4 * kCus
+                 : streamed >= 16384 && (wg >= 4 * kCus || even))
       return 2;
   }
   if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {

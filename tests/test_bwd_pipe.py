@@ -159,6 +159,23 @@ def test_causal_grids_over_one_round(rule):
         assert rule("dk", STUDENT, 128, 128, heads, nq, nk, True) == 0
 
 
+def test_two_blocks_where_they_were_measured(rule):
+    """Under the mask only for the gradients of the narrower head, dK from 4096 streamed rows (of squares, 8192) and dQ from
+    6144 on, over four rounds; without a mask also at equal dims, dQ on grids that fill their rounds."""
+    for kernel, least in (("dk", 8192), ("dq", 12288)):
+        for want, d1, d2 in ((STUDENT, 128, 64), (STUDENT, 192, 64), (STUDENT, 256, 64), (TEACHER, 64, 128), (TEACHER, 64, 256)):
+            assert rule(kernel, want, d1, d2, 32, 65536, 65536, True) == 2
+            assert rule(kernel, want, d1, d2, 32, least, least, True) == 2
+            assert rule(kernel, want, d1, d2, 32, least - 10, least - 10, True) == 0
+            assert rule(kernel, want, d1, d2, 15, 16384, 16384, True) == 0   # 960 workgroups
+        for want, d1, d2 in ((STUDENT, 128, 128), (TEACHER, 128, 128), (STUDENT, 64, 128), (TEACHER, 128, 64)):
+            assert rule(kernel, want, d1, d2, 32, 65536, 65536, True) == 0
+            assert rule(kernel, want, d1, d2, 32, 16384, 16384, False) == 2
+    for causal, blocks in ((True, 0), (False, 2)):   # one full round of equally long blocks
+        assert rule("dq", STUDENT, 192, 64, 8, 8192, 131072, causal) == blocks
+    assert rule("dq", STUDENT, 192, 64, 8, 7424, 131072, False) == rule("dq", STUDENT, 192, 64, 9, 8192, 131072, False) == 0
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("s1,s2,factor", EXTREME_SCALES)
 def test_masked_pairs_at_extreme_scales(gpu_lib, s1, s2, factor):
