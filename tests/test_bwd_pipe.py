@@ -1,7 +1,7 @@
 """The pipelined backward kernels: they compile without spilling, and they give the gradients of the plain kernels bit for
-bit. A head's gradients do not depend on how many heads a call holds, while the kernel that computes them does: at most
-256 workgroups of 128 rows take the pipelined form with one row block per wave, more take the plain one, and many
-workgroups of 256 rows the pipelined form with two."""
+bit. A head's gradients do not depend on how many heads a call holds, while the kernel that computes them does: few
+workgroups take the pipelined form with one row block per wave, more take the plain one, and many that stream enough rows
+the pipelined form with two. That each call below takes the form it is meant to is asked of the host's rule itself."""
 import concurrent.futures as cf
 import os
 import re
@@ -15,6 +15,7 @@ from paper_2606_20005_amd import build, inputs
 from parity_utils import check_grad, to_gpu_f32, upload
 
 ALL = ("dq1", "dk1", "dq2", "dk2")
+STUDENT, TEACHER = ("dq2", "dk2"), ("dq1", "dk1")
 
 
 @pytest.fixture(scope="module")
@@ -56,16 +57,35 @@ def test_no_spills(tmp_path):
     assert seen == 2 * (2 * 2 * (16 + 5) + 10 + 6)
 
 
+# heads, nq, nk, causal; heads of the part of them that takes the plain kernels and of the part that takes one block; the
+# kernels for which this holds, and of which the whole call takes two blocks where they exist (under the mask for the
+# gradients of the narrower head)
+GRIDS = [
+    (512, 70, 16400, False, 300, 30, ("dq",)), (512, 1, 16385, False, 300, 30, ("dq",)),
+    (520, 4101, 70, False, 300, 30, ("dk",)), (130, 4200, 16500, False, 7, 1, ("dk",)),
+    (1024, 70, 6300, True, 600, 30, ("dq",)), (32, 9000, 8300, True, 10, 4, ("dk",)),
+    (32, 12400, 12400, True, 8, 4, ("dq", "dk")), (32, 13500, 13000, True, 8, 4, ("dq", "dk")),
+]
+DIMS = [(128, 128, STUDENT), (128, 64, STUDENT), (64, 128, STUDENT), (192, 64, STUDENT), (256, 64, STUDENT), (128, 64, TEACHER),
+        (64, 192, TEACHER), (64, 64, STUDENT), (64, 64, ALL)]
+
+
+@pytest.mark.parametrize("heads,nq,nk,causal,plain,one,kernels", GRIDS)
+def test_grids_take_the_forms_they_compare(rule, heads, nq, nk, causal, plain, one, kernels):
+    for d1, d2, want in DIMS:
+        own, other = (d2, d1) if want == STUDENT else (d1, d2)
+        two = want != ALL and own + other >= 192 and (not causal or own < other)
+        for k in kernels:
+            assert rule(k, want, d1, d2, heads, nq, nk, causal) == (2 if two else 0), (k, d1, d2, want)
+            assert rule(k, want, d1, d2, plain, nq, nk, causal) == 0, (k, d1, d2, want)
+            assert rule(k, want, d1, d2, one, nq, nk, causal) == 1, (k, d1, d2, want)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("heads,nq,nk,causal", [
-    (512, 70, 16400, False), (512, 70, 16400, True), (512, 1, 16385, False),   # two blocks for dQ
-    (520, 4101, 70, False), (1024, 8200, 33, True), (1024, 8300, 290, True),   # two blocks for dK
-])
-@pytest.mark.parametrize("d1,d2,want", [(128, 128, ("dq2", "dk2")), (128, 64, ("dq2", "dk2")), (64, 128, ("dq2", "dk2")),
-                                        (128, 64, ("dq1", "dk1")), (64, 64, ("dq2", "dk2")), (64, 64, ALL)])
-def test_same_bits_at_every_grid_size(gpu_lib, heads, nq, nk, causal, d1, d2, want):
-    """Ragged tiles, one-row tiles, rows without keys, negative and zero upstream gradients. (64, 64) and all four
-    gradients have no form with two blocks."""
+@pytest.mark.parametrize("heads,nq,nk,causal,plain,one,kernels", GRIDS)
+@pytest.mark.parametrize("d1,d2,want", DIMS)
+def test_same_bits_at_every_grid_size(gpu_lib, heads, nq, nk, causal, plain, one, kernels, d1, d2, want):
+    """Ragged tiles, one-row tiles, rows without keys, negative and zero upstream gradients."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(nq * 1000 + nk)
 
@@ -84,7 +104,7 @@ def test_same_bits_at_every_grid_size(gpu_lib, heads, nq, nk, causal, d1, d2, wa
         return [x for x in out if x is not None]
 
     whole = grads(0, heads)
-    for lo, hi in ((0, 300), (5, 35)):   # the plain kernels; one block
+    for lo, hi in ((0, plain), (heads - one, heads)):
         for a, b in zip(whole, grads(lo, hi)):
             assert torch.isfinite(b).all()
             assert torch.equal(a[:, lo:hi], b), (lo, hi)
@@ -93,10 +113,10 @@ def test_same_bits_at_every_grid_size(gpu_lib, heads, nq, nk, causal, d1, d2, wa
 @pytest.mark.gpu
 @pytest.mark.parametrize("d1,d2,want", [(256, 64, ("dq2", "dk2")), (192, 128, ("dq2", "dk2")), (256, 256, ("dq1", "dk1")),
                                         (128, 128, ALL), (64, 192, ALL), (64, 256, ("dq1", "dk1"))])
-@pytest.mark.parametrize("nq,nk,causal", [(130, 200, True), (40, 33, False)])
+@pytest.mark.parametrize("nq,nk,causal", [(130, 200, True), (40, 33, False), (530, 600, True), (260, 33, False)])
 def test_wide_heads_key_gradients_match_the_plain_kernel(gpu_lib, d1, d2, want, nq, nk, causal):
-    """Where the pipelined kernels run at every size: dK without a dQ in the call takes the plain kernel, which forms
-    the row statistics itself."""
+    """Wide heads take the pipelined kernels from 128 or 256 streamed rows on (the last two sizes); dK without a dQ in the
+    call takes the plain kernel, which forms the row statistics itself."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(d1 * 7 + d2)
     t = [torch.randn(2, 3, n, d, generator=gen, device="cuda").to(torch.bfloat16)
@@ -120,9 +140,6 @@ def test_extreme_scales_take_the_plain_kernels(rule):
         for s1, s2, _ in EXTREME_SCALES:
             assert rule(kernel, ("dq2", "dk2"), 64, 64, 2, 600, 600, True, s1=s1) == 0
             assert rule(kernel, ("dq2", "dk2"), 64, 64, 2, 600, 600, True, s2=s2) == 0
-
-
-STUDENT, TEACHER = ("dq2", "dk2"), ("dq1", "dk1")
 
 
 @pytest.mark.parametrize("d1,d2", [(128, 64), (192, 64), (64, 128), (128, 128)])
