@@ -205,3 +205,41 @@ def test_masked_pairs_at_extreme_scales(gpu_lib, s1, s2, factor):
     got = gpu_lib.bwd(*upload(d), *(to_gpu_f32(x) for x in (kl, lse1, lse2, d["g"])), s1, s2, True, 0, want=ALL)
     for n, x, r in zip(ALL, got, ref):
         check_grad(n, x.cpu().numpy(), r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kernel", ["dq", "dk"])
+def test_reach_of_a_nonfinite_row_with_two_blocks(gpu_lib, kernel):
+    """A wave's tiles serve its 64 resident rows: an infinity in column 5 of a streamed row can reach column 5 of the
+    gradients of the wave's rows that it does not take part in (0 x inf), and nothing else. The rest of the head and the
+    other heads keep their bits."""
+    import torch
+    heads, nq, nk = (1024, 200, 6400) if kernel == "dq" else (32, 8300, 8300)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    t = [torch.randn(1, heads, n, d, generator=gen, device="cuda", dtype=torch.bfloat16)
+         for n, d in ((nq, 128), (nk, 128), (nq, 64), (nk, 64))]
+
+    def grad():
+        stats = gpu_lib.fwd(*t, causal=True)
+        return gpu_lib.bwd(*t, *stats, causal=True, want=STUDENT)[2 if kernel == "dq" else 3]
+
+    clean = grad()
+    at = 170 if kernel == "dq" else 4010   # of 64-row waves [128, 192) and [3968, 4032)
+    if kernel == "dq":
+        t[3][0, 3, nk - nq + at, 5] = float("inf")   # a key that rows 170 to 199 see
+        apart, seen = slice(0, 128), slice(128, at)
+    else:
+        t[2][0, 3, at, 5] = float("inf")             # a row that keys 0 to 4010 are seen by
+        apart, seen = slice(4032, nk), slice(at + 1, 4032)
+    bad = grad()
+    assert not torch.isfinite(bad[0, 3, at]).all()
+    assert torch.equal(clean[0, 3, apart], bad[0, 3, apart])
+    cols = [c for c in range(64) if c != 5]
+    assert torch.equal(clean[0, 3, seen][:, cols], bad[0, 3, seen][:, cols])
+    clean[0, 3], bad[0, 3] = 0.0, 0.0
+    assert torch.equal(clean, bad)
+
+
+def test_reach_is_tested_on_two_blocks(rule):
+    assert rule("dq", STUDENT, 128, 64, 1024, 200, 6400, True) == 2
+    assert rule("dk", STUDENT, 128, 64, 32, 8300, 8300, True) == 2
