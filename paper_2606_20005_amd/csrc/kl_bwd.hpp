@@ -17,8 +17,9 @@
 // contraction, K (for dQ) or Q (for dK), is read from the same LDS tile with
 // gfx950 transpose reads (ds_read_b64_tr_b16). The factor s_t of
 // S_t = s_t Q_t K_t^T is applied once when the gradient tile is written.
-// Where it can, a kernel folds |g| of a row into the row's exponent offsets
-// (fold_row_stats), so that the exponentials are g P directly.
+// With softmax scores |g| of a row is folded into the row's exponent offsets
+// (fold_row_stats), so that the exponentials are |g| P directly; its sign is
+// applied when a row of dQ is written, or to the logit gradients of a tile.
 //
 // MODE bit 0: produce the gradient of "b" (Setting 1); bit 1: of "a" (Setting 2).
 #pragma once
@@ -129,8 +130,8 @@ struct RowsDma {
 };
 
 // The statistics of one row of a streamed tile from its saved values (valid:
-// the row exists), before the tile's fold decision; rows that do not exist
-// or have no allowed key (LSE = -inf) contribute nothing.
+// the row exists), |g| not yet folded; rows that do not exist or have no
+// allowed key (LSE = -inf) contribute nothing.
 __device__ __forceinline__ RowStats tile_row_stats(float la, float lb, float klv, float gv, bool valid) {
   RowStats s{0.f, 0.f, 0.f, 0.f};
   if (valid && la != kNegInf) {
@@ -150,17 +151,17 @@ __device__ __forceinline__ RowStats finish_tile_row_stats(RowStats s) {
 }
 
 // Statistics of a streamed 32-row tile in LDS: [lsa2, lsb2, g, dl][row], |g|
-// folded into lsa2, lsb2, and in *fold whether every stored g is 1 (every g
+// folded into lsa2, lsb2, and in *positive whether every stored g is 1 (every g
 // of the tile >= 0, the usual case): the tile loop may then skip one multiply
 // per distribution and element. Rows at tid >= BS idle.
 template <int BS, int ACT = kActSoftmax>
 __device__ __forceinline__ void stage_row_stats(const float (*raw)[64], int r0, int NQ, bool has_g,
-                                                f32x4 (&dst)[4][BS / 4], int* fold, int tid) {
+                                                f32x4 (&dst)[4][BS / 4], int* positive, int tid) {
   if constexpr (ACT == kActSigmoid) {   // g alone, never folded
     if (tid < BS) {
       float* p = reinterpret_cast<float*>(&dst[0][0]);
       p[2 * BS + tid] = r0 + tid < NQ ? (has_g ? raw[3][tid] : 1.f) : 0.f;
-      if (tid == 0) *fold = 0;
+      if (tid == 0) *positive = 0;
     }
     return;
   }
@@ -175,7 +176,7 @@ __device__ __forceinline__ void stage_row_stats(const float (*raw)[64], int r0, 
     p[1 * BS + tid] = s.lsb2;
     p[2 * BS + tid] = s.g;
     p[3 * BS + tid] = s.dl;
-    if (tid == 0) *fold = any_negative ? 0 : 1;
+    if (tid == 0) *positive = any_negative ? 0 : 1;
   }
 }
 
@@ -187,21 +188,21 @@ __device__ __forceinline__ void stage_row_stats(const float (*raw)[64], int r0, 
 // tile's barrier. kl_bwd_rowstats_kernel forms them for every tile of every
 // head beforehand, with the same arithmetic bit for bit: tile T = head * ntq
 // + t (ntq = ceil(N_Q / 32)) as stats[T][4][32] floats (lsa2, lsb2, g, dl by
-// row, |g| folded, g the sign) and fold[T], whether every sign is positive
-// (the kernel is in kl_bwd_rowstats.hip). The dK kernel then streams each tile's 512 bytes and
-// flag into LDS with its query tile.
+// row, |g| folded, g the sign) and positive[T], whether every sign is positive
+// (the kernel is in kl_bwd_rowstats.hip). The dK kernel then streams each
+// tile's 512 bytes and flag into LDS with its query tile.
 // ----------------------------------------------------------------------------
 constexpr int kRowStatsTile = 32;
 constexpr int kRowStatsTilesPerBlock = 8;
 
 // Direct-to-LDS loads of one prepared tile (512 bytes: two dword loads of the
-// wave) and its fold flag (one lane), issued by one wave.
+// wave) and its sign flag (one lane), issued by one wave.
 struct PreparedStatsDma {
   rsrc_t r_s, r_f;
-  __device__ __forceinline__ PreparedStatsDma(const float* stats, const int* fold, size_t head_tile0, int ntq) {
+  __device__ __forceinline__ PreparedStatsDma(const float* stats, const int* positive, size_t head_tile0, int ntq) {
     const bool on = stats != nullptr;
     r_s = make_rsrc(on ? stats + head_tile0 * 4 * kRowStatsTile : stats, on ? (uint32_t)ntq * 512u : 0u);
-    r_f = make_rsrc(on ? fold + head_tile0 : fold, on ? (uint32_t)ntq * 4u : 0u);
+    r_f = make_rsrc(on ? positive + head_tile0 : positive, on ? (uint32_t)ntq * 4u : 0u);
   }
   __device__ __forceinline__ void issue_stats(int t, float* dst, int lane) const {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -210,18 +211,18 @@ struct PreparedStatsDma {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r_s, (lds_void*)(dst + 64), 4, off + 256u, 0, 0, 0);
 #endif
   }
-  __device__ __forceinline__ void issue(int t, float* dst, int* fold_dst, int lane) const {
+  __device__ __forceinline__ void issue(int t, float* dst, int* positive_dst, int lane) const {
     issue_stats(t, dst, lane);
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (lane == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(r_f, (lds_void*)fold_dst, 4, (uint32_t)t * 4u, 0, 0, 0);
+    if (lane == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(r_f, (lds_void*)positive_dst, 4, (uint32_t)t * 4u, 0, 0, 0);
 #endif
   }
 };
 
-// Logit gradients of one element (raw dot products ra, rb). FOLD: the row's
-// |g| is already folded into the exponent offsets (lsa2, lsb2 lowered by
-// log2 |g|), so the exponentials are g P directly and the sign of g is
-// applied elsewhere; otherwise g multiplies here.
+// Logit gradients of one element (raw dot products ra, rb). With softmax
+// scores |g| is folded into the exponent offsets already (lsa2, lsb2 lowered
+// by log2 |g|) and s.g is the sign: FOLD leaves it to the caller (or knows it
+// to be 1), otherwise it multiplies here. Sigmoid scores multiply by g itself.
 template <bool WANT_A, bool WANT_B, bool FOLD = false, int ACT = kActSoftmax>
 __device__ __forceinline__ void dlogits(float ra, float rb, bool ok, float ca, float cb, float sa, float sb,
                                         const RowStats& s, float& dsa, float& dsb) {
@@ -588,7 +589,7 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
                  const float* __restrict__ kl, const float* __restrict__ lse_a,
                  const float* __restrict__ lse_b, const float* __restrict__ g,
                  void* __restrict__ dKa, void* __restrict__ dKb, int bf16,
-                 const float* __restrict__ pstats, const int* __restrict__ pfold) {
+                 const float* __restrict__ pstats, const int* __restrict__ ppositive) {
   // PD: the head dims may be padded (the rows in memory are dra, drb long);
   // otherwise they are the compile-time ones and the runtime values unused
   if constexpr (!PD) {
@@ -603,7 +604,7 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
   // the same reason as the stages; tile t_begin + 2j uses the first)
   __shared__ float sraw0[4][64];
   __shared__ float sraw1[4][64];
-  __shared__ int sfold[2];                    // per stage: g folded into the statistics
+  __shared__ int spositive[2];                // per stage: whether every sign is positive
 
   // the wave index is uniform: in a scalar register, so are the values derived from it
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
@@ -645,7 +646,7 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
   // prepared statistics (kl_bwd_rowstats_kernel), when the caller made them
   static_assert(C::BS == kRowStatsTile, "prepared statistics come in tiles of the streamed rows");
   const bool pre = ACT == kActSoftmax && pstats != nullptr;
-  const PreparedStatsDma pdma(pre ? pstats : nullptr, pfold, (size_t)bh * ntq, ntq);
+  const PreparedStatsDma pdma(pre ? pstats : nullptr, ppositive, (size_t)bh * ntq, ntq);
 
   const TrOffsets<DA, DB, MODE> tro(lane);
   auto tile = [&](const u32x4* stage, int buf, int t) {
@@ -668,14 +669,15 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
       const int q = r0 + 8 * (i >> 2) + 4 * half + (i & 3);
       return q < NQ && (!CAUSAL || myk <= q + off);
     };
-    // the general path also takes the tiles whose g could not be folded
-    // (a third variant would cost registers everywhere)
+    // the general path, which multiplies by the stored sign, also takes the
+    // tiles with a negative one (a third variant would cost registers
+    // everywhere)
     if constexpr (ACT == kActSigmoid) {
       if (opaque(need_mask))
         bwd_tile<DA, DB, MODE, true, false, ACT>(stage, ka, kb, dka, dkb, ca, cb, sa, sb, lane, stats, ok, tro);
       else
         bwd_tile<DA, DB, MODE, false, false, ACT>(stage, ka, kb, dka, dkb, ca, cb, sa, sb, lane, stats, ok, tro);
-    } else if (opaque(need_mask || !sfold[buf])) {
+    } else if (opaque(need_mask || !spositive[buf])) {
       bwd_tile<DA, DB, MODE, true, false>(stage, ka, kb, dka, dkb, ca, cb, sa, sb, lane, stats, ok, tro);
     } else {
       bwd_tile<DA, DB, MODE, false, true>(stage, ka, kb, dka, dkb, ca, cb, sa, sb, lane, stats, ok, tro);
@@ -688,10 +690,10 @@ kl_bwd_dk_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ K
   // end-of-step wait and barrier. With them, wave 0 streams tile t + 1's
   // statistics and flag straight into their stage during step t.
   auto stats_in = [&](int t, float (*raw)[64], int buf) {
-    if (wave == 0) stage_row_stats<C::BS, ACT>(raw, t * C::BS, NQ, rdma.has_g, sstat[buf], &sfold[buf], tid);
+    if (wave == 0) stage_row_stats<C::BS, ACT>(raw, t * C::BS, NQ, rdma.has_g, sstat[buf], &spositive[buf], tid);
   };
   auto pre_in = [&](int t, int buf) {
-    if (wave == 0) pdma.issue(t, reinterpret_cast<float*>(&sstat[buf][0][0]), &sfold[buf], lane);
+    if (wave == 0) pdma.issue(t, reinterpret_cast<float*>(&sstat[buf][0][0]), &spositive[buf], lane);
   };
   if (t_begin < ntq) {
     dma.issue(rqa, rqb, t_begin * C::BS, st0, wave, dra, drb);

@@ -177,7 +177,7 @@ kl_bwd_fused_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict_
   __shared__ u32x4 ds_a[C::WANT_A ? C::DS_CH : 1];                  // dS tiles
   __shared__ u32x4 ds_b[C::WANT_B ? C::DS_CH : 1];
   __shared__ f32x4 sstat[2][4][C::BS / 4];                          // row statistics of the stages
-  __shared__ int sfold[2];                                          // per stage: g folded into them
+  __shared__ int spositive[2];                                      // per stage: whether every sign is positive
   auto raw_of = [](const u32x4* stage) { return reinterpret_cast<const float (*)[64]>(stage + BC::STAGE); };
 
   // the wave index is uniform: in a scalar register, so are the values derived from it
@@ -370,8 +370,9 @@ kl_bwd_fused_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict_
     float dsa[16], dsb[16];
     asm volatile("" : "+v"(kres_row));
     if (active) {
-      // the general path also takes the tiles whose g could not be folded
-      if (opaque(need_mask || !sfold[buf]))
+      // the general path, which multiplies by the stored sign, also takes the
+      // tiles with a negative one
+      if (opaque(need_mask || !spositive[buf]))
         bwd_dlogits_tile<DA, DB, MODE, true, false, kActSoftmax>(cur, op_a, op_b, ca, cb, sa, sb, ln, stats, ok, dsa,
                                                                  dsb);
       else
@@ -392,7 +393,7 @@ kl_bwd_fused_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict_
       // tile's loads are done
       if (n_atomic >= kDqAtomicsPerBlock) wait_vmem_le<kDqAtomicsPerBlock>();
       else wait_vmem();
-      stage_row_stats<C::BS>(raw_of(nxt), tile_at(i + 1) * C::BS, NQ, rdma.has_g, sstat[buf ^ 1], &sfold[buf ^ 1],
+      stage_row_stats<C::BS>(raw_of(nxt), tile_at(i + 1) * C::BS, NQ, rdma.has_g, sstat[buf ^ 1], &spositive[buf ^ 1],
                              tid);
     }
     wait_lds();
@@ -403,7 +404,7 @@ kl_bwd_fused_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict_
   if (nt > 0) {
     stage_in(tile_at(0), st0);
     wait_vmem();
-    stage_row_stats<C::BS>(raw_of(st0), tile_at(0) * C::BS, NQ, rdma.has_g, sstat[0], &sfold[0], tid);
+    stage_row_stats<C::BS>(raw_of(st0), tile_at(0) * C::BS, NQ, rdma.has_g, sstat[0], &spositive[0], tid);
   }
   wait_vmem();   // key block copies
   __syncthreads();

@@ -25,11 +25,11 @@
 //    Scheduling barriers pin this order: left to itself the compiler forms
 //    all logits, then all vector work (7% slower).
 //  - Measured against the kernels of kl_bwd.hpp (same box, ms, dQ and dK, 32
-//    heads x 16384): d 128/128 student 5.59, 5.93 -> 5.34, 5.64, causal 2.87,
-//    3.07 -> 2.82, 2.98; d 128/64 4.10, 4.39 -> 3.96, 4.07; teacher at 128/128
-//    5.52, 5.88 -> 5.26, 5.52; all four gradients (RB = 1: the accumulators of
-//    both pairs leave no room for two blocks) 8.99, 10.31 -> 8.06, 8.89,
-//    causal 4.72, 5.47 -> 4.26, 4.73. The outputs are the same bit for bit.
+//    heads x 16384): d 128/128 student 5.59, 5.93 -> 5.34, 5.64; d 128/64 4.10,
+//    4.39 -> 3.96, 4.07; teacher at 128/128 5.52, 5.88 -> 5.26, 5.52; all four
+//    gradients (RB = 1: the accumulators of both pairs leave no room for two
+//    blocks) 8.99, 10.31 -> 8.06, 8.89, causal 4.72, 5.47 -> 4.26, 4.73. The
+//    outputs are the same bit for bit. pipe_blocks says where each form runs.
 //
 // Masked pairs: their raw logits are replaced by kBwdMaskedRaw, which gives
 // P = 0 exactly and finite factors at the scales that pipe_scale admits, so
@@ -395,7 +395,7 @@ __global__ void __launch_bounds__(kThreads, 1)
 kl_bwd_dk_pipe_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restrict__ Ka,
                       const uint16_t* __restrict__ Qb, const uint16_t* __restrict__ Kb, int NQ, int NK, float sa,
                       float sb, void* __restrict__ dKa, void* __restrict__ dKb, int bf16,
-                      const float* __restrict__ pstats, const int* __restrict__ pfold) {
+                      const float* __restrict__ pstats, const int* __restrict__ ppositive) {
   using C = PipeCfg<DA, DB, MODE, RB>;
   static_assert(C::BS == kRowStatsTile, "prepared statistics come in tiles of the streamed rows");
   __shared__ u32x4 st0[C::STAGE];
@@ -419,7 +419,7 @@ kl_bwd_dk_pipe_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restric
   }
 
   bool mine = false;
-  for (int t = t_begin + tid; t < ntq; t += kThreads) mine = mine || pfold[(size_t)bh * ntq + t] == 0;
+  for (int t = t_begin + tid; t < ntq; t += kThreads) mine = mine || ppositive[(size_t)bh * ntq + t] == 0;
   const bool negative = __syncthreads_or(mine) != 0;
 
   bf16x8 ka[RB][C::KA], kb[RB][C::KB];
@@ -436,7 +436,7 @@ kl_bwd_dk_pipe_kernel(const uint16_t* __restrict__ Qa, const uint16_t* __restric
   const rsrc_t rqa = make_rsrc(Qa + (size_t)bh * NQ * DA, (uint32_t)NQ * DA * 2u);
   const rsrc_t rqb = make_rsrc(Qb + (size_t)bh * NQ * DB, (uint32_t)NQ * DB * 2u);
   const TileDma<C::BS, C::CA, C::CB> dma(tid);
-  const PreparedStatsDma pdma(pstats, pfold, (size_t)bh * ntq, ntq);
+  const PreparedStatsDma pdma(pstats, ppositive, (size_t)bh * ntq, ntq);
   const TrOffsets<DA, DB, MODE> tro(lane);
 
   PipeState<C> P;

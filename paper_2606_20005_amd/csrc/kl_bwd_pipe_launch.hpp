@@ -100,7 +100,7 @@ hipError_t run_pipe(const BwdArgs& a) {
     const dim3 grid((unsigned)(a.BH * (((DK ? a.NK : a.NQ) + rows - 1) / rows)));
     if constexpr (DK)
       hipLaunchKernelGGL((kl_bwd_dk_pipe_kernel<DA, DB, CAUSAL, MODE, RB>), grid, dim3(kThreads), 0, a.stream, a.Qa,
-                         a.Ka, a.Qb, a.Kb, a.NQ, a.NK, a.sa, a.sb, a.dKa, a.dKb, a.bf16, a.pstats, a.pfold);
+                         a.Ka, a.Qb, a.Kb, a.NQ, a.NK, a.sa, a.sb, a.dKa, a.dKb, a.bf16, a.pstats, a.ppositive);
     else
       hipLaunchKernelGGL((kl_bwd_dq_pipe_kernel<DA, DB, CAUSAL, MODE, RB>), grid, dim3(kThreads), 0, a.stream, a.Qa,
                          a.Ka, a.Qb, a.Kb, a.NQ, a.NK, a.sa, a.sb, a.kl, a.lse_a, a.lse_b, a.g, a.dQa, a.dQb, a.bf16);

@@ -8,7 +8,7 @@ namespace streamkl {
 static __global__ void __launch_bounds__(kRowStatsTile * kRowStatsTilesPerBlock)
 kl_bwd_rowstats_kernel(const float* __restrict__ kl, const float* __restrict__ lse_a,
                        const float* __restrict__ lse_b, const float* __restrict__ g, int NQ, int ntq,
-                       long long tiles, float* __restrict__ stats, int* __restrict__ fold) {
+                       long long tiles, float* __restrict__ stats, int* __restrict__ positive) {
   const int lane = threadIdx.x & 63, r = lane & 31;
   const long long T = (long long)blockIdx.x * kRowStatsTilesPerBlock + (threadIdx.x >> 5);
   const bool live = T < tiles;
@@ -28,7 +28,7 @@ kl_bwd_rowstats_kernel(const float* __restrict__ kl, const float* __restrict__ l
   p[1 * kRowStatsTile + r] = s.lsb2;
   p[2 * kRowStatsTile + r] = s.g;
   p[3 * kRowStatsTile + r] = s.dl;
-  if (r == 0) fold[T] = any_negative ? 0 : 1;
+  if (r == 0) positive[T] = any_negative ? 0 : 1;
 }
 
 static long long rowstats_tiles(int bh, int nq) { return (long long)bh * ((nq + kRowStatsTile - 1) / kRowStatsTile); }
@@ -41,12 +41,12 @@ size_t bwd_rowstats_floats(int bh, int nq) {
 hipError_t launch_bwd_rowstats(BwdArgs& a, float* stats) {
   const int ntq = (a.NQ + kRowStatsTile - 1) / kRowStatsTile;
   const long long tiles = rowstats_tiles(a.BH, a.NQ);
-  int* fold = reinterpret_cast<int*>(stats + (size_t)tiles * 4 * kRowStatsTile);
+  int* positive = reinterpret_cast<int*>(stats + (size_t)tiles * 4 * kRowStatsTile);
   const dim3 grid((unsigned)((tiles + kRowStatsTilesPerBlock - 1) / kRowStatsTilesPerBlock));
   hipLaunchKernelGGL(kl_bwd_rowstats_kernel, grid, dim3(kRowStatsTile * kRowStatsTilesPerBlock), 0, a.stream,
-                     a.kl, a.lse_a, a.lse_b, a.g, a.NQ, ntq, tiles, stats, fold);
+                     a.kl, a.lse_a, a.lse_b, a.g, a.NQ, ntq, tiles, stats, positive);
   a.pstats = stats;
-  a.pfold = fold;
+  a.ppositive = positive;
   return hipGetLastError();
 }
 

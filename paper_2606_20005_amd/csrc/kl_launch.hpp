@@ -34,7 +34,7 @@ struct BwdArgs {
   hipStream_t stream;
   // row statistics prepared by launch_bwd_rowstats for the dK kernel (null: it forms them itself)
   const float* pstats = nullptr;
-  const int* pfold = nullptr;
+  const int* ppositive = nullptr;
 };
 
 // Each returns hipErrorInvalidValue for a head-dim pair it does not hold,
@@ -60,7 +60,7 @@ hipError_t launch_bwd_dk(int da, int db, bool causal, int mode, const BwdArgs& a
 // 128 per 32-row tile plus one int flag per tile.
 size_t bwd_rowstats_floats(int bh, int nq);
 // Prepares them into stats (the flags follow the 128-float tiles) and points
-// a.pstats, a.pfold at them; softmax scores only.
+// a.pstats, a.ppositive at them; softmax scores only.
 hipError_t launch_bwd_rowstats(BwdArgs& a, float* stats);
 hipError_t launch_bwd_dq_m1(int da, int db, bool causal, const BwdArgs& a);
 hipError_t launch_bwd_dq_m2(int da, int db, bool causal, const BwdArgs& a);

@@ -46,7 +46,7 @@ hipError_t launch_bwd_fused_m3(int, int, bool, const BwdArgs&) { return stub(); 
 size_t bwd_rowstats_floats(int bh, int nq) { return (size_t)bh * ((nq + 31) / 32) * 129; }
 hipError_t launch_bwd_rowstats(BwdArgs& a, float* stats) {
   a.pstats = stats;
-  a.pfold = reinterpret_cast<const int*>(stats);
+  a.ppositive = reinterpret_cast<const int*>(stats);
   return stub();
 }
 }  // namespace streamkl

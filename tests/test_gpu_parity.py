@@ -146,10 +146,10 @@ def _signed_g(shape, pattern):
 @pytest.mark.parametrize("strategy", ["separate", "fused"])
 @pytest.mark.parametrize("pattern", ["mixed", "some_tiles", "magnitudes"])
 def test_upstream_gradient_signs(gpu_lib, pattern, strategy):
-    """The kernels fold |g| of a row into its exponent offsets when they can
-    (dQ: every row, the sign applied when written; dK: tiles whose g are all
-    >= 0) and multiply by g otherwise: negative, zero and widely scaled g
-    give the oracle's gradients on either side of that choice."""
+    """The kernels fold |g| of every row into its exponent offsets and apply
+    the sign elsewhere (dQ: when a row is written; dK and fused: in tiles that
+    hold a negative one): negative, zero and widely scaled g give the oracle's
+    gradients, in tiles of either kind."""
     d = inputs.make("tiny", B=1, H=2, n_q=200, n_k=700)
     d["g"] = _signed_g(d["g"].shape, pattern)
     for causal in (False, True):
@@ -165,7 +165,7 @@ def test_dk_prepared_statistics_match_in_kernel_staging(gpu_lib, pattern, n_q, n
     """When a dQ is requested too, the dK kernel streams row statistics that a
     prep kernel wrote into that dQ output beforehand; alone, it forms them
     itself. Same arithmetic: dK bit for bit equal either way, for every g
-    pattern (folded and unfolded tiles, g absent), ragged tails, both
+    pattern (tiles with and without a negative sign, g absent), ragged tails, both
     directions, padded dims and a dQ too small to hold them (3 rows of d = 32:
     in-kernel path on both sides). The dQ written over the prepared values
     equals a dQ-only call bit for bit."""
