@@ -188,9 +188,12 @@ def test_two_blocks_where_they_were_measured(rule):
         for want, d1, d2 in ((STUDENT, 128, 128), (TEACHER, 128, 128), (STUDENT, 64, 128), (TEACHER, 128, 64)):
             assert rule(kernel, want, d1, d2, 32, 65536, 65536, True) == 0
             assert rule(kernel, want, d1, d2, 32, 16384, 16384, False) == 2
-    for causal, blocks in ((True, 0), (False, 2)):   # one full round of equally long blocks
-        assert rule("dq", STUDENT, 192, 64, 8, 8192, 131072, causal) == blocks
-    assert rule("dq", STUDENT, 192, 64, 8, 7424, 131072, False) == rule("dq", STUDENT, 192, 64, 9, 8192, 131072, False) == 0
+    for causal in (False, True):   # rounds of equally long blocks: full ones, under the mask together with dK
+        assert rule("dq", STUDENT, 192, 64, 8, 8192, 131072, causal) == 2
+        assert rule("dq", STUDENT, 192, 64, 8, 7424, 131072, causal) == rule("dq", STUDENT, 192, 64, 9, 8192, 131072, causal) == 0
+        assert rule("dq", STUDENT, 192, 64, 32, 2048, 60000, causal) == (0 if causal else 2)
+        assert rule("dq", STUDENT, 192, 64, 16, 8192, 60000, causal) == (0 if causal else 2)
+    assert rule("dq", STUDENT, 128, 128, 8, 8192, 131072, True) == 0
 
 
 @pytest.mark.gpu
