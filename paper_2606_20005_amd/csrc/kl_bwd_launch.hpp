@@ -41,9 +41,10 @@ hipError_t run_bwd_kernel(bool causal, const BwdArgs& a) {
 // Launches the dQ (DK = false) or dK (DK = true) kernel of gradient mode
 // MODE and activation ACT for the kernel head-dim pair (da, db); the
 // instantiation for padded head dims when the real ones (a.dra, a.drb) are
-// narrower. Where the rule for the sizes picks the pipelined form of the
-// kernel (softmax scores, unpadded head dims; dK with prepared statistics),
-// that one runs instead.
+// narrower. Where the rule for sizes and scales picks the pipelined form of
+// the kernel (softmax scores, unpadded head dims; dK with prepared
+// statistics), that one runs instead. The dQ kernels of unpadded wide heads
+// are then left with the scales that the pipelined form does not take.
 template <int MODE, int ACT, bool DK>
 hipError_t launch_bwd_unit(int da, int db, bool causal, const BwdArgs& a) {
   if constexpr (ACT == kActSoftmax) {
