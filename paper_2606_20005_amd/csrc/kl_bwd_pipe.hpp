@@ -5,10 +5,11 @@
 // the tile loop overlaps the matrix and vector work of neighbouring tiles.
 //
 // What bounds it, and why this form (MI355X, 32 heads, 16K x 16K):
-//  - The chip is power limited here: it clocks down to 1.65-1.8 GHz of 2.4 as
-//    its pipes fill. Removing a third of the dQ kernel's stall cycles alone
-//    gave 2%, so the energy of a tile counts as much as its cycles. Of the
-//    dQ kernel's time the direct-to-LDS loads of the streamed tiles cost 6%,
+//  - The chip is power limited here: the kernels of kl_bwd.hpp clock down to
+//    1.74-1.82 GHz of 2.4 with the matrix pipe busy for 57-65% of the cycles.
+//    Removing a third of the dQ kernel's stall cycles alone gave 2%, so the
+//    energy of a tile counts as much as its cycles. Of the dQ kernel's time
+//    the direct-to-LDS loads of the streamed tiles cost 6%,
 //    half of the operand reads from LDS 1-3% (timing variants without them).
 //    With RB = 2 each operand read from LDS feeds two MFMAs and each streamed
 //    tile 256 rows: both halve.
@@ -30,12 +31,16 @@
 //    gradients (RB = 1: the accumulators of both pairs leave no room for two
 //    blocks) 8.99, 10.31 -> 8.06, 8.89, causal 4.72, 5.47 -> 4.26, 4.73. The
 //    outputs are the same bit for bit. pipe_blocks says where each form runs.
+//    Counters at d 128/128: 1.85-1.93 GHz (two boxes), matrix pipe busy for
+//    56-61% of the cycles, vector pipe 49-50%; 20 and 16 LDS instructions a
+//    32 x 32 block (dK, dQ) instead of 41 and 32, 110 and 103 vector ones
+//    instead of 96 and 94. So the gain is clock: fewer LDS reads for the same
+//    MFMAs.
 //
 // Masked pairs: their raw logits are replaced by kBwdMaskedRaw, which gives
 // P = 0 exactly and finite factors at the scales that pipe_scale admits, so
-// their logit gradients are 0. Before
-// the first tile the pipeline holds a neutral one (every pair masked,
-// operands 0).
+// their logit gradients are 0. Before the first tile the pipeline holds a
+// neutral one (every pair masked, operands 0).
 #pragma once
 
 #include <type_traits>
