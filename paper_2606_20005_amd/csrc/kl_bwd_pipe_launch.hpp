@@ -52,7 +52,8 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 //    1.05 (1.26) below 85%). dQ causal: from 6144 rows on, over four rounds;
 //    square heads of 6K to 12K streamed rows took 0.99 (1.05) with dK alone and
 //    0.97 (1.03) with both, all heads of 2K to 6K 0.99 (1.04) and 1.00 (1.23).
-//    So also where dQ's blocks are of nearly one length, fill their rounds and
+//    dQ without dK lost 1.06 (64 heads, 4385 rows on 14421 keys, d 192/64), so
+//    dQ goes by dK's limits too. So also where dQ's blocks are of nearly one length, fill their rounds and
 //    dK takes two: the last rows of a long context, ms without, with dK, with
 //    both: d 192/64, 8 heads, 8192 rows on 131072 keys 9.92, 9.62, 9.61; d
 //    256/64 11.73, 11.22, 10.96; d 128/64 8.34, 8.23, 7.96; d 192/64, 16 x 8192
@@ -82,8 +83,9 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
     const long long wg = a.BH * ((own + 255) / 256);
     const bool even = 20 * wg >= 19 * ((wg + kCus - 1) / kCus * kCus);
     constexpr bool narrow = MODE == 1 ? DB < DA : DA < DB;
-    if (DK       ? streamed >= 4096 && (causal ? narrow && wg >= 4 * kCus : wg >= 2 * kCus)
-        : causal ? narrow && (wg >= 4 * kCus ? streamed >= 6144 : even && nk >= 8 * nq && pairs >= 4096 * nk)
+    const bool dk_causal = narrow && pairs >= 4096 * nk && a.BH * ((nk + 255) / 256) >= 4 * kCus;
+    if (DK       ? (causal ? dk_causal : streamed >= 4096 && wg >= 2 * kCus)
+        : causal ? dk_causal && (wg >= 4 * kCus ? streamed >= 6144 : even && nk >= 8 * nq)
                  : streamed >= 16384 && (wg >= 4 * kCus || even))
       return 2;
   }

@@ -63,7 +63,7 @@ def test_no_spills(tmp_path):
 GRIDS = [
     (512, 70, 16400, False, 300, 30, ("dq",)), (512, 1, 16385, False, 300, 30, ("dq",)),
     (520, 4101, 70, False, 300, 30, ("dk",)), (130, 4200, 16500, False, 7, 1, ("dk",)),
-    (1024, 70, 6300, True, 600, 30, ("dq",)), (32, 9000, 8300, True, 10, 4, ("dk",)),
+    (8, 8100, 66000, True, 5, 2, ("dq",)), (32, 9000, 8300, True, 10, 4, ("dk",)),
     (32, 12400, 12400, True, 8, 4, ("dq", "dk")), (32, 13500, 13000, True, 8, 4, ("dq", "dk")),
 ]
 DIMS = [(128, 128, STUDENT), (128, 64, STUDENT), (64, 128, STUDENT), (192, 64, STUDENT), (256, 64, STUDENT), (128, 64, TEACHER),
@@ -194,6 +194,8 @@ def test_two_blocks_where_they_were_measured(rule):
         assert rule("dq", STUDENT, 192, 64, 32, 2048, 60000, causal) == (0 if causal else 2)
         assert rule("dq", STUDENT, 192, 64, 16, 8192, 60000, causal) == (0 if causal else 2)
     assert rule("dq", STUDENT, 128, 128, 8, 8192, 131072, True) == 0
+    for heads, nq, nk in ((64, 4385, 14421), (32, 40000, 7000)):   # not without dK
+        assert rule("dq", STUDENT, 192, 64, heads, nq, nk, True) == rule("dk", STUDENT, 192, 64, heads, nq, nk, True) == 0
 
 
 @pytest.mark.gpu
@@ -217,7 +219,7 @@ def test_reach_of_a_nonfinite_row_with_two_blocks(gpu_lib, kernel):
     gradients of the wave's rows that it does not take part in (0 x inf), and nothing else. The rest of the head and the
     other heads keep their bits."""
     import torch
-    heads, nq, nk = (1024, 200, 6400) if kernel == "dq" else (32, 8300, 8300)
+    heads, nq, nk = (32, 12400, 12400) if kernel == "dq" else (32, 8300, 8300)
     gen = torch.Generator(device="cuda").manual_seed(5)
     t = [torch.randn(1, heads, n, d, generator=gen, device="cuda", dtype=torch.bfloat16)
          for n, d in ((nq, 128), (nk, 128), (nq, 64), (nk, 64))]
@@ -229,7 +231,7 @@ def test_reach_of_a_nonfinite_row_with_two_blocks(gpu_lib, kernel):
     clean = grad()
     at = 170 if kernel == "dq" else 4010   # of 64-row waves [128, 192) and [3968, 4032)
     if kernel == "dq":
-        t[3][0, 3, nk - nq + at, 5] = float("inf")   # a key that rows 170 to 199 see
+        t[3][0, 3, nk - nq + at, 5] = float("inf")   # a key that rows from 170 on see
         apart, seen = slice(0, 128), slice(128, at)
     else:
         t[2][0, 3, at, 5] = float("inf")             # a row that keys 0 to 4010 are seen by
@@ -244,5 +246,5 @@ def test_reach_of_a_nonfinite_row_with_two_blocks(gpu_lib, kernel):
 
 
 def test_reach_is_tested_on_two_blocks(rule):
-    assert rule("dq", STUDENT, 128, 64, 1024, 200, 6400, True) == 2
+    assert rule("dq", STUDENT, 128, 64, 32, 12400, 12400, True) == 2
     assert rule("dk", STUDENT, 128, 64, 32, 8300, 8300, True) == 2
