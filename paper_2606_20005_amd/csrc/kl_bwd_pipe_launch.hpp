@@ -66,7 +66,10 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 //    one round, by streamed rows: dK 64-127 1.12 causal, 1.03 not; 128-255
 //    1.03, 0.99; 256-511 0.95, 0.93; 512-1023 0.88. dQ 64-127 1.01; 128-255
 //    0.96, 0.98. Where the old kernel has one wave per SIMD: dK 64-127 1.06,
-//    0.99; 128-255 0.94, 0.97; dQ 0.93 at most, however short.
+//    0.99; 128-255 0.94, 0.97; dQ 0.93 at most, however short. dQ of causal
+//    heads with N_K < N_Q goes by the rows that see a key, the others end at
+//    once: 128-255 1.01, 256 on 0.96 and 0.91 (1 head, 34688 rows on 1920 keys,
+//    d 256/64: backward 0.132 -> 0.103).
 // The rows a workgroup streams are the mean over the grid, a head's allowed
 // pairs over its own rows. Under the causal mask with N_K < N_Q only the last
 // N_K query rows see a key, so that a key streams N_K / 2 of them: two blocks
@@ -91,7 +94,8 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
   }
   if constexpr (kPipeBuilt<DA, DB, MODE, 1, DK>) {
     constexpr bool alone = BwdCfg<DA, DB, MODE>::MINB == 1;
-    if (streamed < (DK ? (alone ? 128 : 256) : (alone ? 0 : 128))) return 0;
+    const long long least = DK ? (alone ? 128 : 256) : alone ? 0 : rows < nq ? 256 : 128;
+    if ((DK || rows == 0 ? streamed : pairs / rows) < least) return 0;
     const long long wg = a.BH * ((own + 127) / 128);
     if (alone || wg <= kCus) return 1;
     if (causal && wg <= 2 * kCus) {

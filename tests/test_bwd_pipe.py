@@ -158,6 +158,9 @@ def test_short_streams_take_the_plain_kernels(rule, d1, d2, alone):
                       (1, int(alone), 0)):
         assert rule("dq", STUDENT, d1, d2, 8, 300, n, False) == dq, n
         assert rule("dk", STUDENT, d1, d2, 8, n, 300, False) == dk, n
+    # rows without a key do not count for dQ
+    assert rule("dq", STUDENT, d1, d2, 1, 30000, 600, True) == rule("dk", STUDENT, d1, d2, 1, 30000, 600, True) == 1
+    assert rule("dq", STUDENT, d1, d2, 1, 30000, 500, True) == int(alone)
 
 
 def test_causal_grids_over_one_round(rule):
