@@ -43,15 +43,19 @@ inline bool pipe_scale(float s) { return s >= 0x1p-80f && s <= 0x1p26f; }
 //    are formed and the other one):
 //      no mask   64 and 128, 192, 256: 0.98, 0.97, 0.95 (1.01); 128 and 128
 //                0.98 (1.02, and one of 1.18), 128 and 64 1.00 (1.05);
-//      causal    64 and 128, 192, 256: 0.98, 0.98, 0.96 (1.03) with the rule
-//                below; 128 and 128 1.01 (1.07), 128 and 64 1.02 (1.09) with
-//                dK alone from 4096 rows on: not taken.
-//    dK: from 4096 rows on, over two rounds of workgroups, causal four.
+//      causal    64 and 128, 192, 256: 0.99, 0.99, 0.97 (1.03) with the rule
+//                below (1196 grids on four boxes); 128 and 128 1.01 (1.07), 128
+//                and 64 1.02 (1.09) with dK alone from 4096 rows on: not taken.
+//    dK: from 4096 rows on, over two rounds of workgroups, causal four. Causal
+//    squares stream from nothing to all rows and gain from 8192 on (4096 to
+//    8192 with 64 and 128, 192: 1.00 (1.05)), unless the other dim is four
+//    times as wide (0.98 (1.00)).
 //    dQ without a mask: from 16384 rows on, over four rounds or on a grid that
 //    fills its last one to 95% (below four rounds 0.98 (1.00) where it does,
-//    1.05 (1.26) below 85%). dQ causal: from 6144 rows on, over four rounds;
-//    square heads of 6K to 12K streamed rows took 0.99 (1.05) with dK alone and
-//    0.97 (1.03) with both, all heads of 2K to 6K 0.99 (1.04) and 1.00 (1.23).
+//    1.05 (1.26) below 85%). dQ causal: from 6144 rows on, over four rounds.
+//    Square heads of 6K to 12K streamed rows took 0.99 (1.05) with dK alone and
+//    0.97 (1.03) with both on two of the boxes, 0.99 (1.03) either way on the
+//    others; all heads of 2K to 6K 0.99 (1.04) and 1.00 (1.23).
 //    dQ without dK lost 1.06 (64 heads, 4385 rows on 14421 keys, d 192/64), so
 //    dQ goes by dK's limits too. So also where dQ's blocks are of nearly one length, fill their rounds and
 //    dK takes two: the last rows of a long context, ms without, with dK, with
@@ -85,8 +89,10 @@ int pipe_blocks(const BwdArgs& a, bool causal) {
   if constexpr (kPipeBuilt<DA, DB, MODE, 2, DK>) {
     const long long wg = a.BH * ((own + 255) / 256);
     const bool even = 20 * wg >= 19 * ((wg + kCus - 1) / kCus * kCus);
-    constexpr bool narrow = MODE == 1 ? DB < DA : DA < DB;
-    const bool dk_causal = narrow && pairs >= 4096 * nk && a.BH * ((nk + 255) / 256) >= 4 * kCus;
+    constexpr int formed = MODE == 1 ? DB : DA, other = MODE == 1 ? DA : DB;   // head dims (two blocks: modes 1 and 2)
+    const bool flat = 10 * pairs >= 6 * nq * nk;   // key blocks of nearly one length, N_K well above N_Q
+    const bool dk_causal = formed < other && a.BH * ((nk + 255) / 256) >= 4 * kCus &&
+                           pairs >= (flat || other >= 4 * formed ? 4096 : 8192) * nk;
     if (DK       ? (causal ? dk_causal : streamed >= 4096 && wg >= 2 * kCus)
         : causal ? dk_causal && (wg >= 4 * kCus ? streamed >= 6144 : even && nk >= 8 * nq)
                  : streamed >= 16384 && (wg >= 4 * kCus || even))

@@ -63,8 +63,8 @@ def test_no_spills(tmp_path):
 GRIDS = [
     (512, 70, 16400, False, 300, 30, ("dq",)), (512, 1, 16385, False, 300, 30, ("dq",)),
     (520, 4101, 70, False, 300, 30, ("dk",)), (130, 4200, 16500, False, 7, 1, ("dk",)),
-    (8, 8100, 66000, True, 5, 2, ("dq",)), (32, 9000, 8300, True, 10, 4, ("dk",)),
-    (32, 12400, 12400, True, 8, 4, ("dq", "dk")), (32, 13500, 13000, True, 8, 4, ("dq", "dk")),
+    (8, 8100, 66000, True, 5, 2, ("dq",)), (32, 17000, 16700, True, 5, 3, ("dq", "dk")),
+    (32, 16400, 16400, True, 4, 3, ("dq", "dk")),
 ]
 DIMS = [(128, 128, STUDENT), (128, 64, STUDENT), (64, 128, STUDENT), (192, 64, STUDENT), (256, 64, STUDENT), (128, 64, TEACHER),
         (64, 192, TEACHER), (64, 64, STUDENT), (64, 64, ALL)]
@@ -180,13 +180,15 @@ def test_causal_grids_over_one_round(rule):
 
 
 def test_two_blocks_where_they_were_measured(rule):
-    """Under the mask only for the gradients of the narrower head, dK from 4096 streamed rows (of squares, 8192) and dQ from
-    6144 on, over four rounds; without a mask also at equal dims, dQ on grids that fill their rounds."""
+    """Under the mask only for the gradients of the narrower head and over four rounds: square heads from 16384 rows on,
+    with a head dim four times as wide from 8192 (dK) and 12288 (dQ) on; without a mask also at equal dims, dQ on grids
+    that fill their rounds."""
     for kernel, least in (("dk", 8192), ("dq", 12288)):
         for want, d1, d2 in ((STUDENT, 128, 64), (STUDENT, 192, 64), (STUDENT, 256, 64), (TEACHER, 64, 128), (TEACHER, 64, 256)):
+            n = least if 256 in (d1, d2) else 16384
             assert rule(kernel, want, d1, d2, 32, 65536, 65536, True) == 2
-            assert rule(kernel, want, d1, d2, 32, least, least, True) == 2
-            assert rule(kernel, want, d1, d2, 32, least - 10, least - 10, True) == 0
+            assert rule(kernel, want, d1, d2, 32, n, n, True) == 2
+            assert rule(kernel, want, d1, d2, 32, n - 10, n - 10, True) == 0
             assert rule(kernel, want, d1, d2, 15, 16384, 16384, True) == 0   # 960 workgroups
         for want, d1, d2 in ((STUDENT, 128, 128), (TEACHER, 128, 128), (STUDENT, 64, 128), (TEACHER, 128, 64)):
             assert rule(kernel, want, d1, d2, 32, 65536, 65536, True) == 0
@@ -222,7 +224,7 @@ def test_reach_of_a_nonfinite_row_with_two_blocks(gpu_lib, kernel):
     gradients of the wave's rows that it does not take part in (0 x inf), and nothing else. The rest of the head and the
     other heads keep their bits."""
     import torch
-    heads, nq, nk = (32, 12400, 12400) if kernel == "dq" else (32, 8300, 8300)
+    heads, nq, nk = 32, 16400, 16400
     gen = torch.Generator(device="cuda").manual_seed(5)
     t = [torch.randn(1, heads, n, d, generator=gen, device="cuda", dtype=torch.bfloat16)
          for n, d in ((nq, 128), (nk, 128), (nq, 64), (nk, 64))]
@@ -249,5 +251,4 @@ def test_reach_of_a_nonfinite_row_with_two_blocks(gpu_lib, kernel):
 
 
 def test_reach_is_tested_on_two_blocks(rule):
-    assert rule("dq", STUDENT, 128, 64, 32, 12400, 12400, True) == 2
-    assert rule("dk", STUDENT, 128, 64, 32, 8300, 8300, True) == 2
+    assert rule("dq", STUDENT, 128, 64, 32, 16400, 16400, True) == rule("dk", STUDENT, 128, 64, 32, 16400, 16400, True) == 2
